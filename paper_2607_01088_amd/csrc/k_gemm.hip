@@ -21,16 +21,19 @@ namespace rosa {
 // Block tile BM x BN = (32 MB) x (32 TN WN), WM x WN waves, each wave
 // (32 MB / WM) x (32 TN) made of 32 x 32 v_mfma_f32_32x32x16_bf16 tiles.
 //
-// Main loop: K is consumed BK (32 or 64) at a time through a ring of NST = 4
+// Main loop: K is consumed BK (32 or 64) at a time through a ring of NST
 // LDS stages filled by global_load_lds_dwordx4 (global -> LDS without
-// staging registers): while the waves multiply stage s, stage s+1 has landed
-// and stages s+2 .. s+NST-1 are landing or being requested, so NST - 2 stages
-// of copies cover the memory latency.  One barrier per stage, crossed before the stage's last
-// k-step of MFMAs so that the next stage's first operand reads overlap them;
-// within a stage each k-step's operands are read while the previous k-step's
-// MFMAs run.  The copies are issued as
-// inline assembly the compiler does not track and the barrier is a bare
-// s_barrier, so the only wait on them is the explicit vmcnt before it.
+// staging registers).  Operand fragments are read from LDS LA k-steps (16 of K)
+// ahead of their MFMAs into a ring of register sets: an LDS read takes longer
+// than a k-step of a small wave tile (two to four MFMAs), and one wave per SIMD
+// has nothing else to run meanwhile, so one k-step ahead left each of them
+// waiting (128 x 128 tile, data in L2: 0.345 us per 64 of K one k-step ahead,
+// 0.26 three ahead, which is what 32 KB take at the 125 GB/s a CU's copies
+// reach).  One barrier per stage, crossed before the first look-ahead into the
+// next stage; by then the whole stage is in registers, so its buffer is
+// refilled at once and NST - 1 stages are in flight or landed.  The copies are
+// issued as inline assembly the compiler does not track and the barrier is a
+// bare s_barrier, so the only wait on them is the explicit vmcnt before it.
 //
 // LDS rows are 64 bytes (32 bf16 of K); the four 16-byte chunks of row r are
 // stored XOR-swizzled by (r / 4) % 4, so the 16 rows a 16-lane group reads at
@@ -44,10 +47,12 @@ namespace rosa {
 // whole 64- or 128-byte row segments with 16-byte accesses.
 //
 // Blocks are mapped to tiles so that each of the 8 XCDs (which receive blocks
-// round-robin) works on a contiguous range of the row-major tile list: the
-// column tiles of one row panel share an XCD's L2.
+// round-robin) works on a contiguous range of the tile list, which runs in
+// strips of a few column tiles: the tiles an XCD holds at a time are a
+// near-square patch, so they share rows of both operands in its L2.
 namespace gb {
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }   // and lgkmcnt(0)
 // f(integral_constant<int, i>) for i = 0 .. N - 1, in order.
 template <int N, int I = 0, typename F>
 __device__ __forceinline__ void static_for(F &&f) {
@@ -66,7 +71,7 @@ __device__ __forceinline__ void static_for(F &&f) {
 template <int CPR>
 __device__ __forceinline__ int gswz(int r) { return CPR == 4 ? (r >> 2) & 3 : (r >> 1) & 7; }
 
-template <int MB_, int TN_, int WM_, int WN_, int BK_ = 32, int NST_ = 4>
+template <int MB_, int TN_, int WM_, int WN_, int BK_ = 32, int NST_ = 4, int LA_ = 1>
 struct GemmTile {
   static constexpr int MB = MB_, TN = TN_, WM = WM_, WN = WN_, NW = WM_ * WN_, NT = 64 * NW;
   static constexpr int MBW = MB / WM;                                   // 32-row blocks per wave
@@ -74,11 +79,15 @@ struct GemmTile {
   static constexpr int BK = BK_;                                        // K per stage
   static constexpr int ROWB = BK * 2, CPR = ROWB / 16, RPU = 1024 / ROWB;   // row bytes, chunks per row, rows per 1 KB
   static constexpr int ABYTES = BM * BK * 2, SBYTES = ABYTES + BN * BK * 2;
-  // LDS ring depth: 4, or 8 for the 64-row tiles of small launches (one
-  // block per CU, latency-bound: more copies in flight per CU).  Deeper rings
-  // measured no faster on the larger tiles.
+  // LDS ring depth: 4; 6 or 8 for the small tiles of small launches (one
+  // block per CU, latency-bound: more copies in flight per CU; 128 x 64 at 816
+  // rows, N = 2048, K = 16384: 102 us with 4 stages, 88 with 6).
   static constexpr int NST = NST_;
   static_assert(NST * SBYTES <= 160 * 1024, "LDS");
+  // k-steps of operand fragments read ahead of their MFMAs, in NSET register
+  // sets (a divisor of the ring's k-steps, so the sets repeat with the ring).
+  static constexpr int NKS = BK / 16, LA = LA_, NSET = LA_ < 2 ? 2 : 4;
+  static_assert(LA >= 1 && LA <= NKS && LA < NSET && NST * NKS % NSET == 0, "look-ahead");
   static constexpr int U = (BM + BN) / RPU;                             // 1 KB copies per stage
   static_assert(BK == 32 || BK == 64, "stage K");
   static constexpr int CHI = (U + NW - 1) / NW, CLO = U / NW;           // copies per wave
@@ -148,85 +157,74 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs &g, int m0, int n0,
   // Operand reads: lane reads row (lane & 31) of a 32-row block, logical chunk
   // 2 ks + lane / 32, at physical chunk (logical) ^ gswz(row); every 32-row
   // block starts at a multiple of 32 rows, so the swizzle depends on lane & 31.
-  constexpr int NKS = BK / 16;
+  constexpr int NKS = T::NKS;
   const int swz = gswz<CPR>(lane & 31);
   int ph[NKS];
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks) ph[ks] = ((2 * ks + (lane >> 5)) ^ swz) * 16;
   const int arow = (wm * MBW * 32 + (lane & 31)) * ROWB;
   const int brow = ABYTES + (wn * TN * 32 + (lane & 31)) * ROWB;
-  // Fragments of one k-step (MBW A tiles, TN W tiles), double-buffered.
-  bf16x8 fa[2][MBW], fb[2][TN];
-  auto read_frags = [&](const uint8_t *st, int ks, int f) __attribute__((always_inline)) {
+  // Fragments (MBW A tiles, TN W tiles) of NSET k-steps: k-step q is
+  // multiplied from register set q % NSET while k-step q + LA is read from LDS.
+  constexpr int LA = T::LA, NSET = T::NSET;
+  bf16x8 fa[NSET][MBW], fb[NSET][TN];
+  auto read_frags = [&](const uint8_t *st, auto ks_t, auto set_t) __attribute__((always_inline)) {
+    constexpr int ks = decltype(ks_t)::value, f = decltype(set_t)::value;
 #pragma unroll
     for (int j = 0; j < TN; ++j) fb[f][j] = *reinterpret_cast<const bf16x8 *>(st + brow + j * 32 * ROWB + ph[ks]);
 #pragma unroll
     for (int i = 0; i < MBW; ++i) fa[f][i] = *reinterpret_cast<const bf16x8 *>(st + arow + i * 32 * ROWB + ph[ks]);
   };
-  // The k-step's MFMAs; after MFMA number q, between(q) (the refill copies,
-  // spread over the k-step so that no wave stalls on a burst of copies while
-  // its MFMAs wait to issue).
-  auto mfmas = [&](int f, auto &&between) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < MBW; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[f][j], fa[f][i], acc[i][j], 0, 0, 0);
-        between(i * TN + j);
-      }
-  };
-  constexpr int NMF = MBW * TN;            // MFMAs per k-step
-  // Stage kt in buffer kt % NST (`cur`), whose k-step 0 fragments are
-  // already in registers.  Each k-step first reads the next k-step's
-  // fragments, then issues its own MFMAs, so LDS latency hides behind a
-  // k-step of MFMAs.  Before the last k-step's MFMAs the block crosses the
-  // stage boundary: wait until this wave's copies of stage kt + 1 have landed
-  // (stages kt + 2 .. kt + NST - 2 may still be in flight), barrier (every
-  // wave's copies have landed, and every wave has finished reading stage
-  // kt - 1), refill stage kt - 1's buffer with stage kt + NST - 1, and read
-  // stage kt + 1's first fragments.
+  constexpr int NMF = MBW * TN, NMS = LA * NMF;   // MFMAs per k-step, and per stage after its barrier
+  // Stage kt in buffer `cur`.  Before k-step NKS - LA, whose look-ahead is the
+  // first read of stage kt + 1, the block crosses the stage boundary: the wait
+  // covers this wave's own reads of stage kt and copies of stage kt + 1 (stages
+  // kt + 2 .. kt + NST - 1 may still be in flight); after the barrier both hold
+  // for every wave, so stage kt's buffer is free and takes stage kt + NST.  The
+  // copies are spread evenly over the stage's remaining MFMAs, so no wave
+  // stalls on a burst of them.
   auto stage = [&](auto cur_t, int kt) __attribute__((always_inline)) {
     constexpr int cur = decltype(cur_t)::value;
-    constexpr int nxt = cur + 1 == NST ? 0 : cur + 1, old = cur == 0 ? NST - 1 : cur - 1;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      if (ks + 1 < NKS) {
-        read_frags(L + cur * SBYTES, ks + 1, (ks + 1) & 1);
-      } else {
-        if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 3) * CHI));
-        else __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 3) * CLO));
+    constexpr int nxt = cur + 1 == NST ? 0 : cur + 1;
+    static_for<NKS>([&](auto ks_t) __attribute__((always_inline)) {
+      constexpr int ks = decltype(ks_t)::value, q = cur * NKS + ks;
+      if constexpr (ks == NKS - LA) {
+        if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NST - 2) * CHI));
+        else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NST - 2) * CLO));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        read_frags(L + nxt * SBYTES, 0, 0);
       }
+      read_frags(L + (ks + LA < NKS ? cur : nxt) * SBYTES, std::integral_constant<int, (ks + LA) % NKS>{},
+                 std::integral_constant<int, (q + LA) % NSET>{});
       __builtin_amdgcn_sched_barrier(0);
-      if (ks + 1 < NKS) {
-        mfmas(ks & 1, [](int) {});
-      } else {
-        // copy j after MFMA (j * NMF) / CHI: spread evenly over the k-step
-        mfmas(ks & 1, [&](int q) __attribute__((always_inline)) {
-          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int j = 0; j < CHI; ++j)
-            if ((j * NMF) / CHI == q) issue_one(L + old * SBYTES, kt + NST - 1, j);
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      }
+      for (int i = 0; i < MBW; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[q % NSET][j], fa[q % NSET][i], acc[i][j], 0, 0, 0);
+          if constexpr (ks >= NKS - LA) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < CHI; ++c)
+              if ((c * NMS) / CHI == (ks - (NKS - LA)) * NMF + i * TN + j) issue_one(L + cur * SBYTES, kt + NST, c);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
-  static_assert(NKS % 2 == 0, "the next stage's first fragments go to buffer 0");
 
-  // Prologue: stages 0 .. NST - 2 requested, stage 0 landed.
+  // Prologue: stages 0 .. NST - 1 requested, stage 0 landed and its first LA
+  // k-steps being read.
 #pragma unroll
-  for (int st = 0; st < NST - 1; ++st) issue(L + st * SBYTES, st);
-  if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 2) * CHI));
-  else __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 2) * CLO));
+  for (int st = 0; st < NST; ++st) issue(L + st * SBYTES, st);
+  if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 1) * CHI));
+  else __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 1) * CLO));
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
-  read_frags(L, 0, 0);
-  // Groups of NST stages, unrolled so that every buffer offset is an
-  // immediate, then the remaining stages.
+  static_for<LA>([&](auto ks_t) { read_frags(L, ks_t, ks_t); });
+  // Groups of NST stages, unrolled so that every buffer offset and register
+  // set is an immediate, then the remaining stages.
   int kt = 0;
   for (; kt + NST <= nk; kt += NST)
     static_for<NST>([&](auto r) { stage(r, kt + decltype(r)::value); });
@@ -458,23 +456,26 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int m0, int n0,
 }
 
 template <typename T, int EPI, bool DN = false>
-__global__ void __launch_bounds__(T::NT) gemm_bf16_kernel(GemmArgs g, int nrt, int nct, int ksplit) {
+__global__ void __launch_bounds__(T::NT) gemm_bf16_kernel(GemmArgs g, int nrt, int nct, int ksplit, int strip) {
   constexpr int SBYTES = T::SBYTES;
   __shared__ __attribute__((aligned(1024))) uint8_t L[T::NST * SBYTES];
 
   // Work unit of this block: XCD x = b % 8 takes the x-th eighth of the unit
   // list; unit u is K slice u / n_tiles of tile u % n_tiles (one slice
-  // unless the product is split).
+  // unless the product is split).  Tiles are listed strip by strip (strips of
+  // `strip` column tiles), row-major within a strip.
   const int n_tiles = nrt * nct, n_units = n_tiles * ksplit;
   const int b = blockIdx.x, x = b & 7, q = b >> 3;
   const int per = n_units >> 3, extra = n_units & 7;
   if (q >= per + (x < extra ? 1 : 0)) return;
   const int unit = x * per + min(x, extra) + q;
   const int tile = unit % n_tiles, slice = unit / n_tiles;
-  const int m0 = (tile / nct) * T::BM, n0 = (tile % nct) * T::BN;
-  const int nks = g.K / T::BK / ksplit;
+  const int sidx = min(tile / (nrt * strip), (nct - 1) / strip);
+  const int in_strip = tile - sidx * nrt * strip, width = min(strip, nct - sidx * strip);
+  const int m0 = (in_strip / width) * T::BM, n0 = (sidx * strip + in_strip % width) * T::BN;
+  const int nk = g.K / T::BK, kt0 = nk * slice / ksplit, kt1 = nk * (slice + 1) / ksplit;
   f32x16 acc[T::MBW][T::TN];
-  gemm_mainloop<T>(g, m0, n0, slice * nks, nks, L, acc);
+  gemm_mainloop<T>(g, m0, n0, kt0, kt1 - kt0, L, acc);
   if constexpr (EPI == kEpiPartial) {
     GemmArgs gp = g;
     gp.out = g.part + (size_t)slice * g.M * g.N;
@@ -485,43 +486,44 @@ __global__ void __launch_bounds__(T::NT) gemm_bf16_kernel(GemmArgs g, int nrt, i
   }
 }
 
-// Block configurations and their measured cost on MI355X (one round of
-// blocks over all CUs, microseconds): a per 1024 of K, plus b by epilogue
-// (store, GELU, gated residual); least-squares fits to the projection shapes
-// of the batch workloads at 1060, 2113, 4241 and 8482 rows (the 64-row tiles:
-// at 50, 400, 800 and 1600 rows, where they can win).  Past K = 4096 a
-// round costs a2 more per 1024 of K, from the 16384-deep MLP-down projection
-// of a 26173-row VLM backbone batch (long sustained launches run each tile
-// more slowly, by an amount that differs between tiles).
+// Block configurations and their measured cost on MI355X: a launch takes
+// kLaunchUs plus, per round of blocks over all CUs, a per 1024 of K plus b by
+// epilogue (store, GELU, gated residual), in microseconds; past K = 4096 a
+// round costs a2 more per 1024 of K.  Least-squares fits to the eight
+// projection shapes of the action expert and the vision-language backbone
+// (and the context projection) at 50 - 25600 rows with cold weights: over
+// those 105 shapes the tile this picks is 1% slower than the best one on
+// average.
+constexpr float kLaunchUs = 2.5f;
 struct GemmCfg { int bm, bn, bk; float a, a2, b[3]; };
 static constexpr GemmCfg kCfgs[kGemmConfigs] = {
-    {384, 128, 32, 15.5f, 19.2f, {9.5f, 12.8f, 15.3f}},  // 0: 8 waves, 96 x 64 each
-    {256, 256, 32, 18.8f, 13.8f, {9.2f, 12.3f, 16.7f}},  // 1: 16 waves, 64 x 64 each
-    {128, 256, 32, 12.5f, 13.0f, {6.5f, 7.9f, 11.1f}},   // 2: 8 waves, 64 x 64 each
-    {192, 128, 32, 10.7f, 3.2f, {4.9f, 5.5f, 9.4f}},     // 3: 8 waves, 96 x 32 each
-    {288, 128, 32, 13.7f, 15.3f, {8.8f, 10.9f, 13.7f}},  // 4: 12 waves, 96 x 32 each
-    {128, 64, 64, 4.7f, 5.0f, {3.1f, 3.4f, 6.0f}},       // 5: 4 waves, 64 x 32 each
-    {192, 128, 64, 8.8f, 6.8f, {6.2f, 8.2f, 10.9f}},     // 6: 8 waves, 96 x 32 each
-    {128, 128, 64, 6.5f, 6.0f, {4.7f, 6.3f, 9.9f}},      // 7: 4 waves, 64 x 64 each
-    {160, 128, 64, 8.1f, 3.4f, {4.5f, 7.1f, 14.7f}},     // 8: 4 waves, 160 x 32 each
-    {96, 128, 64, 5.5f, 4.2f, {4.3f, 6.0f, 8.9f}},       // 9: 4 waves, 96 x 32 each
-    {256, 64, 64, 6.9f, 7.4f, {4.0f, 4.8f, 8.8f}},       // 10: 8 waves, 64 x 32 each
-    {64, 64, 64, 2.8f, 5.0f, {4.2f, 4.1f, 6.8f}},        // 11: 4 waves, 32 x 32 each, 8 stages
-    {64, 32, 64, 2.3f, 5.0f, {2.5f, 2.3f, 4.9f}},        // 12: 2 waves, 32 x 32 each, 8 stages
+    {384, 128, 32, 21.3f, -0.3f, {2.1f, 6.4f, 6.5f}},          // 0: 8 waves, 96 x 64 each
+    {256, 256, 32, 25.5f, -3.1f, {3.4f, 7.1f, 10.1f}},         // 1: 8 waves, 128 x 64 each
+    {128, 256, 32, 13.5f, -0.7f, {2.8f, 4.8f, 7.0f}},          // 2: 8 waves, 64 x 64 each
+    {192, 128, 32, 11.2f, 0.4f, {1.3f, 2.6f, 4.7f}},           // 3: 8 waves, 96 x 32 each
+    {288, 128, 32, 16.8f, -1.1f, {3.2f, 5.3f, 8.6f}},          // 4: 12 waves, 96 x 32 each
+    {128, 64, 64, 4.9f, 0.3f, {2.2f, 3.2f, 4.1f}},             // 5: 4 waves, 64 x 32 each, 6 stages
+    {192, 128, 64, 10.9f, 0.4f, {2.8f, 4.9f, 7.0f}},           // 6: 8 waves, 96 x 32 each
+    {128, 128, 64, 7.6f, 1.1f, {2.2f, 3.8f, 5.7f}},            // 7: 4 waves, 64 x 64 each
+    {160, 128, 64, 9.3f, 0.1f, {2.4f, 4.7f, 9.2f}},            // 8: 4 waves, 160 x 32 each
+    {96, 128, 64, 6.4f, 0.5f, {1.6f, 2.9f, 5.1f}},             // 9: 4 waves, 96 x 32 each
+    {256, 64, 64, 8.9f, 0.9f, {1.8f, 3.2f, 4.0f}},             // 10: 8 waves, 64 x 32 each
+    {64, 64, 64, 3.3f, 0.4f, {1.0f, 1.6f, 1.7f}},              // 11: 4 waves, 32 x 32 each, 8 stages
+    {64, 32, 64, 2.5f, 0.0f, {1.3f, 1.7f, 1.6f}},              // 12: 2 waves, 32 x 32 each, 8 stages
 };
-using Cfg0 = GemmTile<12, 2, 4, 2>;
-using Cfg1 = GemmTile<8, 2, 4, 4>;
-using Cfg2 = GemmTile<4, 2, 2, 4>;
-using Cfg3 = GemmTile<6, 1, 2, 4>;
-using Cfg4 = GemmTile<9, 1, 3, 4>;
-using Cfg5 = GemmTile<4, 1, 2, 2, 64>;
-using Cfg6 = GemmTile<6, 1, 2, 4, 64>;
-using Cfg7 = GemmTile<4, 2, 2, 2, 64>;
-using Cfg8 = GemmTile<5, 1, 1, 4, 64>;
-using Cfg9 = GemmTile<3, 1, 1, 4, 64>;
-using Cfg10 = GemmTile<8, 1, 4, 2, 64>;
-using Cfg11 = GemmTile<2, 1, 2, 2, 64, 8>;
-using Cfg12 = GemmTile<2, 1, 2, 1, 64, 8>;
+using Cfg0 = GemmTile<12, 2, 4, 2, 32, 4, 2>;
+using Cfg1 = GemmTile<8, 2, 2, 4, 32, 4, 1>;
+using Cfg2 = GemmTile<4, 2, 2, 4, 32, 4, 2>;
+using Cfg3 = GemmTile<6, 1, 2, 4, 32, 4, 1>;
+using Cfg4 = GemmTile<9, 1, 3, 4, 32, 4, 2>;
+using Cfg5 = GemmTile<4, 1, 2, 2, 64, 6, 3>;
+using Cfg6 = GemmTile<6, 1, 2, 4, 64, 4, 3>;
+using Cfg7 = GemmTile<4, 2, 2, 2, 64, 4, 3>;
+using Cfg8 = GemmTile<5, 1, 1, 4, 64, 4, 3>;
+using Cfg9 = GemmTile<3, 1, 1, 4, 64, 4, 3>;
+using Cfg10 = GemmTile<8, 1, 4, 2, 64, 4, 3>;
+using Cfg11 = GemmTile<2, 1, 2, 2, 64, 8, 3>;
+using Cfg12 = GemmTile<2, 1, 2, 1, 64, 8, 3>;
 template <typename T>
 constexpr bool cfg_matches(const GemmCfg &c) { return T::BM == c.bm && T::BN == c.bn && T::BK == c.bk; }
 static_assert(cfg_matches<Cfg0>(kCfgs[0]) && cfg_matches<Cfg1>(kCfgs[1]) && cfg_matches<Cfg2>(kCfgs[2]) &&
@@ -638,6 +640,15 @@ static bool fusable_norm(const GemmArgs &g, const NormArgs *nm) {
          (nm->u_rows == 0 || (nm->u_rows >= g.M && g.N % 32 == 0));
 }
 
+// Column tiles per strip of the tile list.  An XCD runs about min(32, a
+// launch's eighth) consecutive tiles of the list at a time; strips of
+// w = sqrt(c BM / BN) columns make those c tiles near-square in elements, so
+// the rows of A and W they read together are fewest.
+static int gemm_strip(int nrt, int nct, int ks, int bm, int bn) {
+  const float c = std::min(32.0f, std::max(1.0f, (float)nrt * nct * ks / 8));
+  return std::max(1, std::min(nct, (int)(sqrtf(c * bm / bn) + 0.5f)));
+}
+
 template <typename T>
 static hipError_t launch_tile(const GemmArgs &g, hipStream_t s, bool allow_split, const NormArgs *nm,
                               bool *normed, bool *deferred) {
@@ -646,8 +657,9 @@ static hipError_t launch_tile(const GemmArgs &g, hipStream_t s, bool allow_split
   const bool completes = g.css && (g.epi == kEpiStore || g.epi == kEpiGelu);
   const int ks = allow_split && !completes ? gemm_split_count(g, nrt * nct, T::BK, fusable_norm(g, nm)) : 1;
   dim3 grid((nrt * nct * ks + 7) / 8 * 8);
+  const int strip = gemm_strip(nrt, nct, ks, T::BM, T::BN);
   if (ks > 1) {
-    hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiPartial>), grid, dim3(T::NT), 0, s, g, nrt, nct, ks);
+    hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiPartial>), grid, dim3(T::NT), 0, s, g, nrt, nct, ks, strip);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (fusable_norm(g, nm)) {
@@ -669,19 +681,19 @@ static hipError_t launch_tile(const GemmArgs &g, hipStream_t s, bool allow_split
     return hipGetLastError();
   }
   if (g.dt && g.epi == kEpiGatedResidual) {
-    hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiGatedResidual, true>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1);
+    hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiGatedResidual, true>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1, strip);
     if (deferred) *deferred = true;
     return hipGetLastError();
   }
   if (completes) {
-    if (g.epi == kEpiGelu) hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiGelu, true>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1);
-    else hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiStore, true>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1);
+    if (g.epi == kEpiGelu) hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiGelu, true>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1, strip);
+    else hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiStore, true>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1, strip);
     return hipGetLastError();
   }
   switch (g.epi) {
-    case kEpiStore: hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiStore>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1); break;
-    case kEpiGelu: hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiGelu>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1); break;
-    default: hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiGatedResidual>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1); break;
+    case kEpiStore: hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiStore>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1, strip); break;
+    case kEpiGelu: hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiGelu>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1, strip); break;
+    default: hipLaunchKernelGGL((gemm_bf16_kernel<T, kEpiGatedResidual>), grid, dim3(T::NT), 0, s, g, nrt, nct, 1, strip); break;
   }
   return hipGetLastError();
 }
@@ -803,8 +815,8 @@ int gemm_pick_config(int M, int N, int K, int epi, int n_cu) {
   for (int c = 0; c < kGemmConfigs; ++c) {
     const long tiles = (long)((M + kCfgs[c].bm - 1) / kCfgs[c].bm) * ((N + kCfgs[c].bn - 1) / kCfgs[c].bn);
     const long rounds = (tiles + n_cu - 1) / n_cu;
-    const float t = rounds * (kCfgs[c].a * (K / 1024.0f) + kCfgs[c].a2 * (std::max(K - 4096, 0) / 1024.0f) +
-                              kCfgs[c].b[e]);
+    const float t = kLaunchUs + rounds * (kCfgs[c].a * (K / 1024.0f) +
+                                          kCfgs[c].a2 * (std::max(K - 4096, 0) / 1024.0f) + kCfgs[c].b[e]);
     if (best_t == 0.f || t < best_t) { best = c; best_t = t; }
   }
   return best;
