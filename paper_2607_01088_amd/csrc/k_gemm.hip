@@ -4,10 +4,11 @@
 //
 // Epilogues fuse what follows each projection: plain store (QKV), tanh-GELU
 // (MLP up), and the gated residual h += gate * C whose gate row is the
-// row's flow-time modulation (attention output and MLP down).  Launches with
-// few tiles (few rows) may split K over several blocks per tile: each block
-// stores its slice's fp32 product (kEpiPartial) and a second kernel sums the
-// slices in order and applies the epilogue.
+// row's flow-time modulation (attention output and MLP down).  Smaller launches
+// may split K over several blocks per tile: each block stores its slice's
+// fp32 product (kEpiPartial) and a second kernel sums the slices in order and
+// applies the epilogue, taking the next norm with it.  A few tens of rows run
+// in a kernel of their own (gemm_direct_kernel).
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -522,8 +523,8 @@ using Cfg7 = GemmTile<4, 2, 2, 2, 64, 4, 3>;
 using Cfg8 = GemmTile<5, 1, 1, 4, 64, 4, 3>;
 using Cfg9 = GemmTile<3, 1, 1, 4, 64, 4, 3>;
 using Cfg10 = GemmTile<8, 1, 4, 2, 64, 4, 3>;
-using Cfg11 = GemmTile<2, 1, 2, 2, 64, 8, 3>;
-using Cfg12 = GemmTile<2, 1, 2, 1, 64, 8, 3>;
+using Cfg11 = GemmTile<2, 1, 2, 2, 64, 8, 1>;
+using Cfg12 = GemmTile<2, 1, 2, 1, 64, 8, 1>;
 template <typename T>
 constexpr bool cfg_matches(const GemmCfg &c) { return T::BM == c.bm && T::BN == c.bn && T::BK == c.bk; }
 static_assert(cfg_matches<Cfg0>(kCfgs[0]) && cfg_matches<Cfg1>(kCfgs[1]) && cfg_matches<Cfg2>(kCfgs[2]) &&
@@ -570,68 +571,60 @@ __global__ void __launch_bounds__(256) gemm_split_reduce_kernel(GemmArgs g, int 
 
 // The same sum for a gated-residual product, fused with the modulated
 // RMSNorm of the updated rows (the norm that reads them next).  One block per
-// row, four columns per thread (N <= kFusedNormMax): sum the KS slices in
-// slice order, apply the gated residual exactly as above, write the row back
-// to h, and normalize it into u (row sum of squares: per wave, then the four
-// wave sums in wave order), so a split product needs no separate norm launch.
-template <int KS>
+// row, NV pieces of four columns per thread (piece v: columns 1024 v + 4 thread): sum
+// the KS slices in slice order, apply the gated residual exactly as above,
+// write the row back to h, and normalize it into u (row sum of squares: per
+// thread over its pieces in order, per wave, then the four wave sums in wave
+// order), so a split product needs no separate norm launch.
+template <int KS, int NV>
 __global__ void __launch_bounds__(256) gemm_split_reduce_norm_kernel(GemmArgs g, NormArgs nm) {
-  static_assert(kFusedNormMax == 4 * 256, "four columns per thread");
+  static_assert(NV * 1024 <= kFusedNormMax, "columns per row");
   __shared__ float wsum[4];
-  const int row = blockIdx.x, i = threadIdx.x * 4;
+  const int row = blockIdx.x;
   const int d = g.N;
   const size_t slice = (size_t)g.M * g.N;
   const int mod = g.rowmod[row];
   float *hr = reinterpret_cast<float *>(g.out) + (size_t)row * g.ldo;
-  float4 hv = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (i < d) {
-    const float *pr = g.part + (size_t)row * g.N + i;
-    f32x4 p[KS];
+  f32x4 hv[NV];
+  float sq = 0.f;
 #pragma unroll
-    for (int s2 = 0; s2 < KS; ++s2) p[s2] = *reinterpret_cast<const f32x4 *>(pr + s2 * slice);
-    const float4 gt = *reinterpret_cast<const float4 *>(g.gate + (size_t)mod * g.gate_stride + i);
-    hv = *reinterpret_cast<const float4 *>(hr + i);
-    f32x4 a = p[0];
+  for (int v = 0; v < NV; ++v) {
+    const int i = v * 1024 + threadIdx.x * 4;
+    hv[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (i < d) {
+      const float *pr = g.part + (size_t)row * g.N + i;
+      f32x4 p[KS];
 #pragma unroll
-    for (int s2 = 1; s2 < KS; ++s2) { a[0] += p[s2][0]; a[1] += p[s2][1]; a[2] += p[s2][2]; a[3] += p[s2][3]; }
-    hv.x = hv.x + gt.x * a[0];
-    hv.y = hv.y + gt.y * a[1];
-    hv.z = hv.z + gt.z * a[2];
-    hv.w = hv.w + gt.w * a[3];
-    *reinterpret_cast<float4 *>(hr + i) = hv;
+      for (int s2 = 0; s2 < KS; ++s2) p[s2] = *reinterpret_cast<const f32x4 *>(pr + s2 * slice);
+      const f32x4 gt = *reinterpret_cast<const f32x4 *>(g.gate + (size_t)mod * g.gate_stride + i);
+      hv[v] = *reinterpret_cast<const f32x4 *>(hr + i);
+      f32x4 a = p[0];
+#pragma unroll
+      for (int s2 = 1; s2 < KS; ++s2) { a[0] += p[s2][0]; a[1] += p[s2][1]; a[2] += p[s2][2]; a[3] += p[s2][3]; }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) hv[v][k] = hv[v][k] + gt[k] * a[k];
+      *reinterpret_cast<f32x4 *>(hr + i) = hv[v];
+    }
+    sq += hv[v][0] * hv[v][0] + hv[v][1] * hv[v][1] + hv[v][2] * hv[v][2] + hv[v][3] * hv[v][3];
   }
-  const float ss = wave_sum(hv.x * hv.x + hv.y * hv.y + hv.z * hv.z + hv.w * hv.w);
+  const float ss = wave_sum(sq);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
   __syncthreads();
   const float r = 1.0f / sqrtf((((wsum[0] + wsum[1]) + wsum[2]) + wsum[3]) / (float)d + nm.eps);
-  if (i < d) {
-    const float *mrow = nm.modtab + (size_t)mod * nm.mod_stride;
-    const float4 a = *reinterpret_cast<const float4 *>(mrow + nm.scale_off + i);
-    const float4 b = *reinterpret_cast<const float4 *>(mrow + nm.shift_off + i);
-    bf16x4 o;
-    o[0] = (bf16)(hv.x * r * (1.0f + a.x) + b.x);
-    o[1] = (bf16)(hv.y * r * (1.0f + a.y) + b.y);
-    o[2] = (bf16)(hv.z * r * (1.0f + a.z) + b.z);
-    o[3] = (bf16)(hv.w * r * (1.0f + a.w) + b.w);
-    const size_t off = nm.u_rows > 0 ? kb32_offset(nm.u_rows, row, i) : (size_t)row * d + i;
-    *reinterpret_cast<bf16x4 *>(reinterpret_cast<bf16 *>(nm.u) + off) = o;
+  const float *mrow = nm.modtab + (size_t)mod * nm.mod_stride;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int i = v * 1024 + threadIdx.x * 4;
+    if (i < d) {
+      const f32x4 a = *reinterpret_cast<const f32x4 *>(mrow + nm.scale_off + i);
+      const f32x4 b = *reinterpret_cast<const f32x4 *>(mrow + nm.shift_off + i);
+      bf16x4 o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = (bf16)(hv[v][k] * r * (1.0f + a[k]) + b[k]);
+      const size_t off = nm.u_rows > 0 ? kb32_offset(nm.u_rows, row, i) : (size_t)row * d + i;
+      *reinterpret_cast<bf16x4 *>(reinterpret_cast<bf16 *>(nm.u) + off) = o;
+    }
   }
-}
-
-// K slices for a launch of n_tiles tiles of BK-deep stages (1: no split).
-// A product whose slice reduction also takes the norm that follows it
-// (fused) costs no extra launch, so it splits up to a whole round of blocks
-// (kSplitMinTilesNorm tiles); others only below kSplitMinTiles.
-int gemm_split_count(const GemmArgs &g, int n_tiles, int bk, bool fused) {
-  // K = 1024 products are too short for the saving to pay for the second launch.
-  if (!g.part || n_tiles >= (fused ? kSplitMinTilesNorm : kSplitMinTiles) || g.K < 2048 || g.N % 4 || g.ldo % 4)
-    return 1;
-  const int nk = g.K / bk;
-  const int most_blocks = fused ? std::max(256, 2 * kSplitMinTilesNorm) : 256;
-  for (int ks = kSplitMax; ks >= 2; ks /= 2)
-    if (n_tiles * ks <= most_blocks && nk % ks == 0 && nk / ks >= 4 && (size_t)ks * g.M * g.N <= g.part_floats)
-      return ks;
-  return 1;
 }
 
 // Whether a split gated-residual product can take the norm that follows it.
@@ -649,13 +642,26 @@ static int gemm_strip(int nrt, int nct, int ks, int bm, int bn) {
   return std::max(1, std::min(nct, (int)(sqrtf(c * bm / bn) + 0.5f)));
 }
 
+template <int NV>
+static void launch_reduce_norm(const GemmArgs &g, const NormArgs &nm, int ks, hipStream_t s) {
+  const dim3 grid(g.M), block(256);
+  switch (ks) {
+    case 2: hipLaunchKernelGGL((gemm_split_reduce_norm_kernel<2, NV>), grid, block, 0, s, g, nm); break;
+    case 3: hipLaunchKernelGGL((gemm_split_reduce_norm_kernel<3, NV>), grid, block, 0, s, g, nm); break;
+    case 4: hipLaunchKernelGGL((gemm_split_reduce_norm_kernel<4, NV>), grid, block, 0, s, g, nm); break;
+    case 5: hipLaunchKernelGGL((gemm_split_reduce_norm_kernel<5, NV>), grid, block, 0, s, g, nm); break;
+    case 6: hipLaunchKernelGGL((gemm_split_reduce_norm_kernel<6, NV>), grid, block, 0, s, g, nm); break;
+    case 7: hipLaunchKernelGGL((gemm_split_reduce_norm_kernel<7, NV>), grid, block, 0, s, g, nm); break;
+    default: hipLaunchKernelGGL((gemm_split_reduce_norm_kernel<8, NV>), grid, block, 0, s, g, nm); break;
+  }
+}
+
 template <typename T>
-static hipError_t launch_tile(const GemmArgs &g, hipStream_t s, bool allow_split, const NormArgs *nm,
-                              bool *normed, bool *deferred) {
+static hipError_t launch_tile(const GemmArgs &g, hipStream_t s, int ks, const NormArgs *nm, bool *normed,
+                              bool *deferred) {
   const int nrt = (g.M + T::BM - 1) / T::BM, nct = (g.N + T::BN - 1) / T::BN;
-  // A launch that completes a deferred norm is never split.
   const bool completes = g.css && (g.epi == kEpiStore || g.epi == kEpiGelu);
-  const int ks = allow_split && !completes ? gemm_split_count(g, nrt * nct, T::BK, fusable_norm(g, nm)) : 1;
+  if (ks < 1 || ks > kSplitMax || (ks > 1 && (completes || !g.part || g.K / T::BK < ks))) return hipErrorInvalidValue;
   dim3 grid((nrt * nct * ks + 7) / 8 * 8);
   const int strip = gemm_strip(nrt, nct, ks, T::BM, T::BN);
   if (ks > 1) {
@@ -663,12 +669,8 @@ static hipError_t launch_tile(const GemmArgs &g, hipStream_t s, bool allow_split
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (fusable_norm(g, nm)) {
-      const dim3 ngrid(g.M);
-      switch (ks) {
-        case 2: hipLaunchKernelGGL(gemm_split_reduce_norm_kernel<2>, ngrid, dim3(256), 0, s, g, *nm); break;
-        case 4: hipLaunchKernelGGL(gemm_split_reduce_norm_kernel<4>, ngrid, dim3(256), 0, s, g, *nm); break;
-        default: hipLaunchKernelGGL(gemm_split_reduce_norm_kernel<kSplitMax>, ngrid, dim3(256), 0, s, g, *nm); break;
-      }
+      if (g.N <= 1024) launch_reduce_norm<1>(g, *nm, ks, s);
+      else launch_reduce_norm<2>(g, *nm, ks, s);
       if (normed) *normed = true;
       return hipGetLastError();
     }
@@ -698,38 +700,288 @@ static hipError_t launch_tile(const GemmArgs &g, hipStream_t s, bool allow_split
   return hipGetLastError();
 }
 
-static hipError_t launch_cfg(const GemmArgs &g, int cfg, hipStream_t s, bool allow_split,
-                             const NormArgs *nm = nullptr, bool *normed = nullptr, bool *deferred = nullptr) {
+static hipError_t launch_cfg(const GemmArgs &g, int cfg, int ks, hipStream_t s, const NormArgs *nm = nullptr,
+                             bool *normed = nullptr, bool *deferred = nullptr) {
   if (g.M <= 0) return hipSuccess;
   if (g.K % 128 != 0 || g.N % 8 != 0 || g.a_rows < g.M) return hipErrorInvalidValue;
   switch (cfg) {
-    case 0: return launch_tile<Cfg0>(g, s, allow_split, nm, normed, deferred);
-    case 1: return launch_tile<Cfg1>(g, s, allow_split, nm, normed, deferred);
-    case 2: return launch_tile<Cfg2>(g, s, allow_split, nm, normed, deferred);
-    case 3: return launch_tile<Cfg3>(g, s, allow_split, nm, normed, deferred);
-    case 4: return launch_tile<Cfg4>(g, s, allow_split, nm, normed, deferred);
-    case 5: return launch_tile<Cfg5>(g, s, allow_split, nm, normed, deferred);
-    case 6: return launch_tile<Cfg6>(g, s, allow_split, nm, normed, deferred);
-    case 7: return launch_tile<Cfg7>(g, s, allow_split, nm, normed, deferred);
-    case 8: return launch_tile<Cfg8>(g, s, allow_split, nm, normed, deferred);
-    case 9: return launch_tile<Cfg9>(g, s, allow_split, nm, normed, deferred);
-    case 10: return launch_tile<Cfg10>(g, s, allow_split, nm, normed, deferred);
-    case 11: return launch_tile<Cfg11>(g, s, allow_split, nm, normed, deferred);
-    case 12: return launch_tile<Cfg12>(g, s, allow_split, nm, normed, deferred);
+    case 0: return launch_tile<Cfg0>(g, s, ks, nm, normed, deferred);
+    case 1: return launch_tile<Cfg1>(g, s, ks, nm, normed, deferred);
+    case 2: return launch_tile<Cfg2>(g, s, ks, nm, normed, deferred);
+    case 3: return launch_tile<Cfg3>(g, s, ks, nm, normed, deferred);
+    case 4: return launch_tile<Cfg4>(g, s, ks, nm, normed, deferred);
+    case 5: return launch_tile<Cfg5>(g, s, ks, nm, normed, deferred);
+    case 6: return launch_tile<Cfg6>(g, s, ks, nm, normed, deferred);
+    case 7: return launch_tile<Cfg7>(g, s, ks, nm, normed, deferred);
+    case 8: return launch_tile<Cfg8>(g, s, ks, nm, normed, deferred);
+    case 9: return launch_tile<Cfg9>(g, s, ks, nm, normed, deferred);
+    case 10: return launch_tile<Cfg10>(g, s, ks, nm, normed, deferred);
+    case 11: return launch_tile<Cfg11>(g, s, ks, nm, normed, deferred);
+    case 12: return launch_tile<Cfg12>(g, s, ks, nm, normed, deferred);
     default: return hipErrorInvalidValue;
   }
 }
 
+// ------------------------------------------------------------------ bf16 GEMM for few rows
+// At a few tens of rows a projection is a chain of latencies: launch, the
+// weights' way from HBM, the operands' way through LDS stage by stage, and a
+// second launch where K was split over blocks.  Here a block of KG waves owns
+// a (16 MR) x (16 NC) tile and its waves split K: each loads its share of A and
+// W straight into registers (v_mfma_f32_16x16x32_bf16 operands: 16 rows x 32 of
+// K are one contiguous 1 KB of a kb32 operand), PF steps of 32 of K ahead, so
+// with small shares every load is in flight at once and no barrier stands in the
+// loop.  What the epilogue reads (residual, gate, scale and shift rows, the
+// deferred norm's sums) is requested before the loop too.  The partial products
+// meet in LDS and are summed in wave order.
+template <int MR, int NC, int KG, int PF, int EPI, bool DN>
+__global__ void __launch_bounds__(64 * KG) gemm_direct_kernel(GemmArgs g, int nrt, int nct, int strip) {
+  constexpr int BM = 16 * MR, BN = 16 * NC, NTH = 64 * KG;
+  constexpr int LDR = BN + 4;               // floats per staged row
+  constexpr int Q = BM * BN / 4, NE = (Q + NTH - 1) / NTH;   // 4-column pieces of the tile, per thread
+  static_assert(!DN || BN % 32 == 0, "the deferred norm's sums cover 32 columns");
+  static_assert(NTH >= 8 * BM, "eight threads per row sum the deferred norm's parts");
+  __shared__ __attribute__((aligned(16))) float red[KG * BM * LDR];
+  __shared__ float rms[DN && EPI != kEpiGatedResidual ? BM : 1];
+  const int n_tiles = nrt * nct;
+  const int b = blockIdx.x, x = b & 7, q = b >> 3;
+  const int per = n_tiles >> 3, extra = n_tiles & 7;
+  if (q >= per + (x < extra ? 1 : 0)) return;
+  const int tile = x * per + min(x, extra) + q;
+  const int sidx = min(tile / (nrt * strip), (nct - 1) / strip);
+  const int in_strip = tile - sidx * nrt * strip, width = min(strip, nct - sidx * strip);
+  const int m0 = (in_strip / width) * BM, n0 = (sidx * strip + in_strip % width) * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int kg = __builtin_amdgcn_readfirstlane(tid >> 6) % KG;
+  // This wave's share of K, in steps of 32.
+  const int T = g.K >> 5, lo = T * kg / KG, n = T * (kg + 1) / KG - lo;
+  const size_t as = (size_t)g.a_rows * 64, ws = (size_t)g.N * 64;   // bytes per 32 of K
+  const char *Ab = reinterpret_cast<const char *>(g.a) + lo * as;
+  const char *Wb = reinterpret_cast<const char *>(g.wt) + lo * ws;
+  // Lane holds row lane % 16 of each 16-row block, K values 8 (lane / 16) .. + 7.
+  // Rows past M (columns past N) re-read the last one; their results are never stored.
+  uint32_t ao[MR], wo[NC];
+#pragma unroll
+  for (int i = 0; i < MR; ++i) ao[i] = (uint32_t)min(m0 + 16 * i + (lane & 15), g.M - 1) * 64 + (lane >> 4) * 16;
+#pragma unroll
+  for (int j = 0; j < NC; ++j) wo[j] = (uint32_t)min(n0 + 16 * j + (lane & 15), g.N - 1) * 64 + (lane >> 4) * 16;
+  bf16x8 fa[PF][MR], fw[PF][NC];
+  f32x4 acc[MR][NC];
+#pragma unroll
+  for (int i = 0; i < MR; ++i)
+#pragma unroll
+    for (int j = 0; j < NC; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) fw[p][j] = *reinterpret_cast<const bf16x8 *>(Wb + wo[j]);
+#pragma unroll
+    for (int i = 0; i < MR; ++i) fa[p][i] = *reinterpret_cast<const bf16x8 *>(Ab + ao[i]);
+    Ab += as;
+    Wb += ws;
+  };
+  auto mma = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MR; ++i)
+#pragma unroll
+      for (int j = 0; j < NC; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[p][j], fa[p][i], acc[i][j], 0, 0, 0);
+  };
+#pragma unroll
+  for (int p = 0; p < PF; ++p)
+    if (p < n) load(p);
+  // The epilogue's inputs of this thread's pieces (piece e: row e / (BN / 4),
+  // columns 4 (e % (BN / 4)) .. + 3).
+  f32x4 hv[NE], gt[NE], mv[NE];
+  float ssp = 0.f;
+#pragma unroll
+  for (int e0 = 0; e0 < NE; ++e0) {
+    const int e = e0 * NTH + tid, row = m0 + e / (BN / 4), col = n0 + e % (BN / 4) * 4;
+    hv[e0] = gt[e0] = mv[e0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (e < Q && row < g.M && col < g.N) {
+      if constexpr (EPI == kEpiGatedResidual) {
+        const size_t mo = (size_t)g.rowmod[row] * g.gate_stride + col;
+        hv[e0] = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(g.out) + (size_t)row * g.ldo + col);
+        gt[e0] = *reinterpret_cast<const f32x4 *>(g.gate + mo);
+        if constexpr (DN) mv[e0] = *reinterpret_cast<const f32x4 *>(g.dscale + mo);
+      } else if constexpr (DN) {
+        mv[e0] = *reinterpret_cast<const f32x4 *>(g.cshift + (size_t)g.rowmod[row] * g.cshift_stride + col);
+      }
+    }
+  }
+  if constexpr (DN && EPI != kEpiGatedResidual) {
+    // Eight threads per row sum its parts (cparts = 8 nv): thread p of them parts nv p .. + nv - 1.
+    const int nv = g.cparts >> 3, row = min(m0 + min(tid >> 3, BM - 1), g.M - 1);
+    const float *sp = g.css + (size_t)row * g.cparts + (tid & 7) * nv;
+    for (int v = 0; v < nv; ++v) ssp += sp[v];
+  }
+  int t = 0;
+  for (; t + 2 * PF <= n; t += PF) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      mma(p);
+      __builtin_amdgcn_sched_barrier(0);
+      load(p);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < PF; ++p)
+    if (t + p < n) {
+      mma(p);
+      if (t + PF + p < n) load(p);
+    }
+#pragma unroll
+  for (int p = 0; p < PF; ++p)
+    if (t + PF + p < n) mma(p);
+  // Lane holds row lane % 16, columns 4 (lane / 16) .. + 3 of each 16 x 16 block.
+  float *mine = red + kg * BM * LDR;
+#pragma unroll
+  for (int i = 0; i < MR; ++i)
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+      *reinterpret_cast<f32x4 *>(mine + (16 * i + (lane & 15)) * LDR + 16 * j + 4 * (lane >> 4)) = acc[i][j];
+  if constexpr (DN && EPI != kEpiGatedResidual) {
+    ssp += __shfl_xor(ssp, 1, 64);
+    ssp += __shfl_xor(ssp, 2, 64);
+    ssp += __shfl_xor(ssp, 4, 64);
+    if ((tid & 7) == 0 && (tid >> 3) < BM) rms[tid >> 3] = 1.0f / sqrtf(ssp / (float)g.cd + g.ceps);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e0 = 0; e0 < NE; ++e0) {
+    const int e = e0 * NTH + tid;
+    if (Q % NTH != 0 && e >= Q) break;      // whole waves: Q is a multiple of 64
+    const int r = e / (BN / 4), c = e % (BN / 4) * 4, row = m0 + r, col = n0 + c;
+    const bool in = row < g.M && col < g.N;
+    f32x4 v = *reinterpret_cast<const f32x4 *>(red + r * LDR + c);
+#pragma unroll
+    for (int s = 1; s < KG; ++s) {
+      const f32x4 p = *reinterpret_cast<const f32x4 *>(red + (s * BM + r) * LDR + c);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] += p[k];
+    }
+    if constexpr (EPI == kEpiGatedResidual) {
+      f32x4 h;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) h[k] = hv[e0][k] + gt[e0][k] * v[k];
+      if (in) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(g.out) + (size_t)row * g.ldo + col) = h;
+      if constexpr (DN) {
+        float q2 = 0.f;
+        if (in) {
+          bf16x4 tv;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) tv[k] = (bf16)(h[k] * (1.0f + mv[e0][k]));
+          *reinterpret_cast<bf16x4 *>(reinterpret_cast<bf16 *>(g.dt) + kb32_offset(g.dt_rows, row, col)) = tv;
+          q2 = fmaf(h[3], h[3], fmaf(h[2], h[2], fmaf(h[1], h[1], h[0] * h[0])));
+        }
+        // Eight consecutive threads hold the row's 32 columns.
+        q2 += __shfl_xor(q2, 1, 64);
+        q2 += __shfl_xor(q2, 2, 64);
+        q2 += __shfl_xor(q2, 4, 64);
+        if ((tid & 7) == 0 && in) g.dss[(size_t)row * (g.N >> 5) + (col >> 5)] = q2;
+      }
+    } else {
+      bf16x4 o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float a = v[k];
+        if constexpr (DN) a = fmaf(a, rms[r], mv[e0][k]);
+        if constexpr (EPI == kEpiGelu) a = gelu_tanh_f(a);
+        o[k] = (bf16)a;
+      }
+      const size_t off = g.out_rows > 0 ? kb32_offset(g.out_rows, row, col) : (size_t)row * g.ldo + col;
+      if (in) *reinterpret_cast<bf16x4 *>(reinterpret_cast<bf16 *>(g.out) + off) = o;
+    }
+  }
+}
+
+template <int MR, int NC, int KG, int PF>
+static hipError_t launch_direct(const GemmArgs &g, hipStream_t s, bool *deferred) {
+  constexpr int BM = 16 * MR, BN = 16 * NC;
+  if (g.K % 32 || g.N % 32 || g.a_rows < g.M) return hipErrorInvalidValue;
+  const int nrt = (g.M + BM - 1) / BM, nct = (g.N + BN - 1) / BN;
+  const dim3 grid((nrt * nct + 7) / 8 * 8), block(64 * KG);
+  const int strip = gemm_strip(nrt, nct, 1, BM, BN);
+  if (g.epi == kEpiGatedResidual) {
+    if (g.dt) {
+      hipLaunchKernelGGL((gemm_direct_kernel<MR, NC, KG, PF, kEpiGatedResidual, true>), grid, block, 0, s, g, nrt, nct, strip);
+      if (deferred) *deferred = true;
+    } else {
+      hipLaunchKernelGGL((gemm_direct_kernel<MR, NC, KG, PF, kEpiGatedResidual, false>), grid, block, 0, s, g, nrt, nct, strip);
+    }
+  } else if (g.epi == kEpiGelu) {
+    if (g.css) hipLaunchKernelGGL((gemm_direct_kernel<MR, NC, KG, PF, kEpiGelu, true>), grid, block, 0, s, g, nrt, nct, strip);
+    else hipLaunchKernelGGL((gemm_direct_kernel<MR, NC, KG, PF, kEpiGelu, false>), grid, block, 0, s, g, nrt, nct, strip);
+  } else {
+    if (g.css) hipLaunchKernelGGL((gemm_direct_kernel<MR, NC, KG, PF, kEpiStore, true>), grid, block, 0, s, g, nrt, nct, strip);
+    else hipLaunchKernelGGL((gemm_direct_kernel<MR, NC, KG, PF, kEpiStore, false>), grid, block, 0, s, g, nrt, nct, strip);
+  }
+  return hipGetLastError();
+}
+
+// The direct tiles of the default path and their cost (one round of blocks,
+// as kCfgs): at 50 rows the four projections of the pi0 shape take 5.0 (QKV),
+// 5.3 (O), 5.3 (MLP-up) and 8.6 us (MLP-down) with them, the best LDS tiles 6.1,
+// 8.3 and 6.6 and 9.7 us (the second and fourth K-split and reduced).  Past one
+// round the LDS tiles win (MLP-up at 132 rows 9.3 against 7.2 us).
+struct DirectCfg { int bm, bn; float a, b; };
+constexpr int kDirectConfigs = 2;
+static constexpr DirectCfg kDirect[kDirectConfigs] = {
+    {16, 32, 1.65f, -0.5f},   // 16 waves
+    {32, 32, 1.75f, 0.7f},    // 8 waves
+};
+
 static int device_cu_count();
+
+// Cost of an unsplit launch (kCfgs), microseconds.
+static float tile_cost(int c, int M, int N, float K, float b, int slices, int n_cu) {
+  const long tiles = (long)((M + kCfgs[c].bm - 1) / kCfgs[c].bm) * ((N + kCfgs[c].bn - 1) / kCfgs[c].bn) * slices;
+  const long rounds = (tiles + n_cu - 1) / n_cu;
+  return kLaunchUs + rounds * (kCfgs[c].a * (K / 1024.0f) + kCfgs[c].a2 * (std::max(K - 4096.0f, 0.f) / 1024.0f) + b);
+}
+
+// Tile and K slices of a launch on the default path: the cheapest of the
+// direct tiles while they fill at most one round (with a workspace only: they
+// sum K in another order), of every LDS tile unsplit and, with a workspace, split over 2 .. kSplitMax slices of at
+// least 5 stages.  A slice's block costs its share of K plus 1.8 us; the launch
+// that sums the slices costs kReduceUs plus 1.5 us per million outputs and
+// slice (fit to 60 - 3000 rows, K = 2048 - 16384; the choice is 3% off the
+// best measured one on average).  An unsplit gated residual whose norm the
+// reduction would have taken pays for that norm: a launch of its own, or the
+// deferred norm's share of two epilogues.
+struct GemmChoice { int cfg, ks; };       // cfg >= kGemmConfigs: a direct tile
+static GemmChoice gemm_choose(const GemmArgs &g, int n_cu, const NormArgs *nm, bool can_defer) {
+  const int e = g.epi < 0 || g.epi > 2 ? 2 : g.epi;
+  const bool completes = g.css && (g.epi == kEpiStore || g.epi == kEpiGelu);
+  const bool fuse = fusable_norm(g, nm);
+  const float mn = (float)g.M * (float)g.N * 1e-6f;
+  const float norm_us = fuse ? (can_defer ? 2.5f : 4.3f + 0.55f * mn) : 0.f;
+  GemmChoice best{0, 1};
+  float best_t = 0.f;
+  if (g.part && g.N % 32 == 0 && g.K % 32 == 0)
+    for (int c = 0; c < kDirectConfigs; ++c) {
+      const long tiles = (long)((g.M + kDirect[c].bm - 1) / kDirect[c].bm) * ((g.N + kDirect[c].bn - 1) / kDirect[c].bn);
+      if (tiles > n_cu) continue;
+      // A deferred norm costs a direct tile little: its epilogues' rows load ahead of the products.
+      const float t = kLaunchUs + kDirect[c].a * (g.K / 1024.0f) + kDirect[c].b + (fuse && can_defer ? 0.7f : norm_us);
+      if (best_t == 0.f || t < best_t) { best = {kGemmConfigs + c, 1}; best_t = t; }
+    }
+  for (int c = 0; c < kGemmConfigs; ++c) {
+    const float t1 = tile_cost(c, g.M, g.N, (float)g.K, kCfgs[c].b[e], 1, n_cu) + norm_us;
+    if (best_t == 0.f || t1 < best_t) { best = {c, 1}; best_t = t1; }
+    if (!g.part || completes || g.N % 4 || g.ldo % 4 || g.K < 2048) continue;
+    for (int ks = 2; ks <= kSplitMax; ++ks) {
+      if (g.K / kCfgs[c].bk / ks < 5 || (size_t)ks * g.M * g.N > g.part_floats) break;
+      const float t = tile_cost(c, g.M, g.N, (float)g.K / ks, 1.8f, ks, n_cu) + (fuse ? 2.5f : 3.1f) + 1.5f * mn * ks;
+      if (t < best_t) { best = {c, ks}; best_t = t; }
+    }
+  }
+  return best;
+}
 
 // Whether launch_gemm(g, true, s, force_cfg, then_norm) with g.dt set takes
 // the deferred norm (an unsplit gated-residual launch) for these sizes.
 bool gemm_defers(const GemmArgs &g, int force_cfg, const NormArgs *then_norm) {
   if (g.M <= 0 || g.epi != kEpiGatedResidual) return false;
-  if (force_cfg >= 0) return true;
-  const int c = gemm_pick_config(g.M, g.N, g.K, g.epi, device_cu_count());
-  const int n_tiles = ((g.M + kCfgs[c].bm - 1) / kCfgs[c].bm) * ((g.N + kCfgs[c].bn - 1) / kCfgs[c].bn);
-  return gemm_split_count(g, n_tiles, kCfgs[c].bk, fusable_norm(g, then_norm)) == 1;
+  return force_cfg >= 0 || gemm_choose(g, device_cu_count(), then_norm, true).ks == 1;
 }
 
 // Shift halves of deferred norms: one thread per output column of one layer's
@@ -804,23 +1056,6 @@ hipError_t launch_shift_proj(const float *modtab, int mod_stride, int n_mod, int
   return hipGetLastError();
 }
 
-// A forced configuration never splits K: every configuration then computes
-// each output with the same instruction sequence.
-hipError_t launch_gemm_cfg(const GemmArgs &g, int cfg, hipStream_t s) { return launch_cfg(g, cfg, s, false); }
-
-int gemm_pick_config(int M, int N, int K, int epi, int n_cu) {
-  const int e = epi < 0 || epi > 2 ? 2 : epi;
-  int best = 0;
-  float best_t = 0.f;
-  for (int c = 0; c < kGemmConfigs; ++c) {
-    const long tiles = (long)((M + kCfgs[c].bm - 1) / kCfgs[c].bm) * ((N + kCfgs[c].bn - 1) / kCfgs[c].bn);
-    const long rounds = (tiles + n_cu - 1) / n_cu;
-    const float t = kLaunchUs + rounds * (kCfgs[c].a * (K / 1024.0f) +
-                                          kCfgs[c].a2 * (std::max(K - 4096, 0) / 1024.0f) + kCfgs[c].b[e]);
-    if (best_t == 0.f || t < best_t) { best = c; best_t = t; }
-  }
-  return best;
-}
 
 template <int EPI>
 __device__ __forceinline__ void epilogue_f32(const GemmArgs &g, int row, int col, float v) {
@@ -900,8 +1135,11 @@ hipError_t launch_gemm(const GemmArgs &g, bool bf16_mode, hipStream_t s, int for
     const int n_cu = device_cu_count();
     if ((g.dt || g.css) && (g.N % 32 != 0 || (g.css && (g.cparts <= 0 || g.cparts % 8 || g.cparts > 32 || g.cd <= 0))))
       return hipErrorInvalidValue;
-    if (force_cfg >= 0) return launch_cfg(g, force_cfg, s, false, nullptr, nullptr, deferred);
-    return launch_cfg(g, gemm_pick_config(g.M, g.N, g.K, g.epi, n_cu), s, true, then_norm, normed, deferred);
+    if (force_cfg >= 0) return launch_cfg(g, force_cfg, 1, s, nullptr, nullptr, deferred);
+    const GemmChoice c = gemm_choose(g, n_cu, then_norm, g.dt != nullptr);
+    if (c.cfg == kGemmConfigs) return launch_direct<1, 2, 16, 4>(g, s, deferred);
+    if (c.cfg == kGemmConfigs + 1) return launch_direct<2, 2, 8, 4>(g, s, deferred);
+    return launch_cfg(g, c.cfg, c.ks, s, then_norm, normed, deferred);
   }
   if (g.dt || g.css) return hipErrorInvalidValue;   // bf16 only
   dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);

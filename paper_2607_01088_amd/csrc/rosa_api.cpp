@@ -988,6 +988,10 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
         return launch_setup_rows(d_reqs, n, d_tau_idx, p.Kmax, D.A, b->row_req, b->rowmod, p.M0, b->x, b->stream);
       });
     const int nl = (int)p.lanes.size();
+    // The products may sum K in other orders (slices over blocks) only in
+    // calls too small for two lanes: a request's actions are then the same
+    // whatever number of lanes a larger call runs.
+    const bool split_ok = n < 2 * kMinLaneRequests;
     // Deferred norms: every unsplit output projection and MLP-down leaves t
     // and the row sums of squares for the next product, which completes the
     // norm; the shift halves are computed once per call, when some launch of
@@ -999,7 +1003,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
         for (int k = 0; k < p.Kmax && !defer_on; ++k) {
           if (ln.m[k] == 0 || ln.m[k] > kDeferMaxRows) continue;
           GemmArgs t{};
-          if (nl == 1) { t.part = b->gemm_part; t.part_floats = b->gemm_part_floats; }
+          if (split_ok) { t.part = b->gemm_part; t.part_floats = b->gemm_part_floats; }
           t.M = ln.m[k]; t.N = D.d; t.ldo = D.d; t.epi = kEpiGatedResidual;
           const NormArgs nm{b->modtab, D.mod_stride, 0, 0, D.eps, b->u, b->kb_rows};
           for (int K2 : {D.o_dim, D.dff}) {
@@ -1064,7 +1068,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
             });
           if (e != hipSuccess) break;
           GemmArgs gq{};
-          if (nl == 1) { gq.part = b->gemm_part; gq.part_floats = b->gemm_part_floats; }
+          if (split_ok) { gq.part = b->gemm_part; gq.part_floats = b->gemm_part_floats; }
           gq.a = u; gq.lda = D.d; gq.a_rows = R; gq.wt = (uint8_t *)b->wt_qkv + (size_t)l * D.qkv_dim * D.d * es;
           gq.M = M; gq.N = D.qkv_dim; gq.K = D.d; gq.epi = kEpiStore; gq.out = qkv; gq.ldo = D.qkv_dim;
           if (t_ready) defer_in(gq, l, 0);
@@ -1074,7 +1078,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
           e = run_attention(b, p, ln, k, l, b->qkv, b->o, st, b->kb_rows);
           if (e != hipSuccess) break;
           GemmArgs go{};
-          if (nl == 1) { go.part = b->gemm_part; go.part_floats = b->gemm_part_floats; }
+          if (split_ok) { go.part = b->gemm_part; go.part_floats = b->gemm_part_floats; }
           go.a = o; go.lda = D.o_dim; go.a_rows = R; go.wt = (uint8_t *)b->wt_o + (size_t)l * D.d * D.o_dim * es;
           go.M = M; go.N = D.d; go.K = D.o_dim; go.epi = kEpiGatedResidual; go.out = h; go.ldo = D.d;
           go.gate = b->modtab + base + 2 * D.d; go.gate_stride = D.mod_stride; go.rowmod = rowmod;
@@ -1089,7 +1093,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
             });
           if (e != hipSuccess) break;
           GemmArgs gu{};
-          if (nl == 1) { gu.part = b->gemm_part; gu.part_floats = b->gemm_part_floats; }
+          if (split_ok) { gu.part = b->gemm_part; gu.part_floats = b->gemm_part_floats; }
           gu.a = u; gu.lda = D.d; gu.a_rows = R; gu.out_rows = R; gu.wt = (uint8_t *)b->wt_up + (size_t)l * D.dff * D.d * es;
           gu.M = M; gu.N = D.dff; gu.K = D.d; gu.epi = kEpiGelu; gu.out = g; gu.ldo = D.dff;
           if (t_ready) defer_in(gu, l, D.qkv_dim);
@@ -1097,7 +1101,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
           e = timed(b, kcGemmUp, [&] { return launch_gemm(gu, b->bf16, st, b->gemm_cfg); });
           if (e != hipSuccess) break;
           GemmArgs gd{};
-          if (nl == 1) { gd.part = b->gemm_part; gd.part_floats = b->gemm_part_floats; }
+          if (split_ok) { gd.part = b->gemm_part; gd.part_floats = b->gemm_part_floats; }
           gd.a = g; gd.lda = D.dff; gd.a_rows = R; gd.wt = (uint8_t *)b->wt_down + (size_t)l * D.d * D.dff * es;
           gd.M = M; gd.N = D.d; gd.K = D.dff; gd.epi = kEpiGatedResidual; gd.out = h; gd.ldo = D.d;
           gd.gate = b->modtab + base + 5 * D.d; gd.gate_stride = D.mod_stride; gd.rowmod = rowmod;

@@ -147,10 +147,11 @@ struct GemmArgs {
   void *out; int ldo;        // kEpiStore / kEpiGelu: activation dtype; kEpiGatedResidual: fp32 h
   int out_rows;              // bf16 kEpiStore / kEpiGelu: 0 row-major (ldo), else kb32 planes of out_rows rows
   const float *gate; int gate_stride; const int32_t *rowmod;  // gate = gate[rowmod[m]*gate_stride + n]
-  // Optional fp32 workspace of part_floats floats.  When a launch would have
-  // fewer than kSplitMinTiles tiles (few rows), K is split over up to
-  // kSplitMax blocks per tile: each writes its slice's product here, and a
-  // second kernel sums the slices in order and applies the epilogue.
+  // Optional fp32 workspace of part_floats floats.  With it K may be split
+  // over up to kSplitMax blocks per tile where that is cheaper: each writes
+  // its slice's product here, and a second kernel sums the slices in order and
+  // applies the epilogue.  Without it every output is one MFMA sequence over K
+  // whatever the tile.
   float *part; size_t part_floats;
   // Deferred modulated RMSNorm (bf16, unsplit launches only).  A
   // kEpiGatedResidual launch with dt set also leaves, for the rows it
@@ -165,8 +166,6 @@ struct GemmArgs {
   void *dt; int dt_rows; float *dss; const float *dscale;
   const float *css; int cparts, cd; float ceps; const float *cshift; int cshift_stride;
 };
-constexpr int kSplitMinTiles = 64;
-constexpr int kSplitMinTilesNorm = 128;
 constexpr int kSplitMax = 8;
 // The modulated RMSNorm that consumes the rows a gated-residual projection
 // has just updated: u[m] = RMSNorm(h[m]) (1 + scale) + shift, scale and shift
@@ -181,7 +180,7 @@ struct NormArgs {
 // then_norm (kEpiGatedResidual, bf16, N <= kFusedNormMax), a product whose K
 // is split has the norm fused into the kernel that sums its slices; *normed
 // tells the caller whether that happened (else it launches the norm itself).
-constexpr int kFusedNormMax = 1024;
+constexpr int kFusedNormMax = 2048;
 // A gated-residual launch with dt set that is not split this way runs
 // unsplit with the deferred norm's outputs (*deferred = true).
 hipError_t launch_gemm(const GemmArgs &g, bool bf16, hipStream_t s, int force_cfg = -1,
@@ -195,11 +194,10 @@ bool gemm_defers(const GemmArgs &g, int force_cfg, const NormArgs *then_norm);
 hipError_t launch_shift_proj(const float *modtab, int mod_stride, int n_mod, int L, int layer_stride, int q_off,
                              int u_off, int d, const void *wq, int Nq, const void *wu, int Nu, float *S,
                              hipStream_t s);
-// bf16 GEMM with a given block configuration (an index into the launcher's
-// table of kGemmConfigs tiles, from 384 x 128 down to 64 x 32).
+// Block configurations of the bf16 GEMM (tiles from 384 x 128 down to 64 x 32).
+// A forced configuration never splits K, so every one computes each output
+// with the same instruction sequence.
 constexpr int kGemmConfigs = 13;
-hipError_t launch_gemm_cfg(const GemmArgs &g, int cfg, hipStream_t s);
-int gemm_pick_config(int M, int N, int K, int epi, int n_cu);
 
 // Prefix producer rows.  row_job[row]: the job of stacked row `row`.
 // h[row] = the job's embedding row (bf16 or fp32 in, fp32 out), d % 4 == 0.

@@ -74,6 +74,8 @@ struct rosa_prefill {
   float *zeros = nullptr, *ones = nullptr;   // [d]: zero shift and scale, unit gate
   int32_t *rowmod = nullptr;                 // [max_tokens] zeros
   float *part_o = nullptr, *part_ml = nullptr;
+  float *gemm_part = nullptr;                // bf16: K-slice products of split projections
+  size_t gemm_part_floats = 0;
   // Rotary position embedding of the queries and keys (rope_base > 0): the
   // (cos, sin) table for positions below max_tokens, refreshed per call.
   double rope_base = 0.0;
@@ -375,6 +377,10 @@ rosa_status rosa_prefill_create(const rosa_vlm_config *cfg, const rosa_vlm_weigh
     h->rowmod = palloc<int32_t>(h, T, e);
     h->rope_base = cfg->rope_base;
     if (h->rope_base > 0.0) h->rope_tab = palloc<float>(h, T * h->hd, e);   // T positions x hd/2 (cos, sin)
+    h->gemm_part_floats = h->bf16 ? std::min<size_t>((size_t)kSplitMax * T * std::max(h->qkv_dim, std::max(h->dff, h->d)),
+                                                     (size_t)16 << 20)
+                                  : 0;
+    if (h->gemm_part_floats) h->gemm_part = palloc<float>(h, h->gemm_part_floats, e);
     h->part_o = palloc<float>(h, (size_t)kAttnMaxSlots * kAttnQB * h->hd, e);
     h->part_ml = palloc<float>(h, (size_t)kAttnMaxSlots * kAttnQB * 2, e);
 
@@ -463,13 +469,23 @@ rosa_status rosa_prefill_run(rosa_prefill *h, const rosa_prefix_job *jobs, int32
       for (int i = 0; i < n; ++i) max_p = std::max(max_p, jobs[i].prefix_len);
       e = ptimed(h, pcRope, [&] { return launch_prefill_rope_table(h->rope_tab, max_p, h->hd, h->rope_base, s); });
     }
-    for (int l = 0; l < h->L && e == hipSuccess; ++l) {
-      e = ptimed(h, pcNorm, [&] {
+    // Every norm reads the rows a residual projection has just updated (the
+    // first one the embeddings) and is the same plain RMSNorm; u_ready: a split
+    // projection's slice reduction has taken it.
+    const NormArgs plain_norm{h->zeros, 0, 0, 0, h->cfg.rms_eps, h->u, h->kb_rows};
+    bool u_ready = false;
+    auto norm = [&]() -> hipError_t {
+      if (u_ready) { u_ready = false; return hipSuccess; }
+      return ptimed(h, pcNorm, [&] {
         return launch_modnorm(h->h, M, h->d, h->cfg.rms_eps, h->zeros, 0, 0, 0, h->rowmod, h->u, h->bf16, s,
                               h->kb_rows);
       });
+    };
+    for (int l = 0; l < h->L && e == hipSuccess; ++l) {
+      e = norm();
       if (e != hipSuccess) break;
       GemmArgs gq{};
+      gq.part = h->gemm_part; gq.part_floats = h->gemm_part_floats;
       gq.a = h->u; gq.lda = h->d; gq.a_rows = h->kb_rows; gq.wt = (uint8_t *)h->wt_qkv + (size_t)l * h->qkv_dim * h->d * es;
       gq.M = M; gq.N = h->qkv_dim; gq.K = h->d; gq.epi = kEpiStore; gq.out = h->qkv; gq.ldo = h->qkv_dim;
       e = ptimed(h, pcGemmQKV, [&] { return launch_gemm(gq, h->bf16, s, h->gemm_cfg); });
@@ -503,34 +519,31 @@ rosa_status rosa_prefill_run(rosa_prefill *h, const rosa_prefix_job *jobs, int32
         });
       if (e != hipSuccess) break;
       GemmArgs go{};
+      go.part = h->gemm_part; go.part_floats = h->gemm_part_floats;
       go.a = h->o; go.lda = h->o_dim; go.a_rows = h->kb_rows; go.wt = (uint8_t *)h->wt_o + (size_t)l * h->d * h->o_dim * es;
       go.M = M; go.N = h->d; go.K = h->o_dim; go.epi = kEpiGatedResidual; go.out = h->h; go.ldo = h->d;
       go.gate = h->ones; go.gate_stride = 0; go.rowmod = h->rowmod;
-      e = ptimed(h, pcGemmO, [&] { return launch_gemm(go, h->bf16, s, h->gemm_cfg); });
+      e = ptimed(h, pcGemmO, [&] { return launch_gemm(go, h->bf16, s, h->gemm_cfg, &plain_norm, &u_ready); });
       if (e != hipSuccess) break;
-      e = ptimed(h, pcNorm, [&] {
-        return launch_modnorm(h->h, M, h->d, h->cfg.rms_eps, h->zeros, 0, 0, 0, h->rowmod, h->u, h->bf16, s,
-                              h->kb_rows);
-      });
+      e = norm();
       if (e != hipSuccess) break;
       GemmArgs gu{};
+      gu.part = h->gemm_part; gu.part_floats = h->gemm_part_floats;
       gu.a = h->u; gu.lda = h->d; gu.a_rows = h->kb_rows; gu.out_rows = h->kb_rows; gu.wt = (uint8_t *)h->wt_up + (size_t)l * h->dff * h->d * es;
       gu.M = M; gu.N = h->dff; gu.K = h->d; gu.epi = kEpiGelu; gu.out = h->g; gu.ldo = h->ldg;
       e = ptimed(h, pcGemmUp, [&] { return launch_gemm(gu, h->bf16, s, h->gemm_cfg); });
       if (e != hipSuccess) break;
       GemmArgs gd{};
+      gd.part = h->gemm_part; gd.part_floats = h->gemm_part_floats;
       gd.a = h->g; gd.lda = h->ldg; gd.a_rows = h->kb_rows; gd.wt = (uint8_t *)h->wt_down + (size_t)l * h->d * h->dff * es;
       gd.M = M; gd.N = h->d; gd.K = h->dff; gd.epi = kEpiGatedResidual; gd.out = h->h; gd.ldo = h->d;
       gd.gate = h->ones; gd.gate_stride = 0; gd.rowmod = h->rowmod;
-      e = ptimed(h, pcGemmDown, [&] { return launch_gemm(gd, h->bf16, s, h->gemm_cfg); });
+      e = ptimed(h, pcGemmDown, [&] { return launch_gemm(gd, h->bf16, s, h->gemm_cfg, &plain_norm, &u_ready); });
     }
     if (h->context && e == hipSuccess) {
       // Final RMSNorm, one projection for every head layer, then each layer's
       // [K | V] column block into the caches.
-      e = ptimed(h, pcNorm, [&] {
-        return launch_modnorm(h->h, M, h->d, h->cfg.rms_eps, h->zeros, 0, 0, 0, h->rowmod, h->u, h->bf16, s,
-                              h->kb_rows);
-      });
+      e = norm();
       GemmArgs gc{};
       gc.a = h->u; gc.lda = h->d; gc.a_rows = h->kb_rows; gc.wt = h->wt_ctx;
       gc.M = M; gc.N = h->ctx_dim; gc.K = h->d; gc.epi = kEpiStore; gc.out = h->ctx; gc.ldo = h->ctx_dim;

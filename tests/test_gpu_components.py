@@ -168,6 +168,41 @@ def test_projection_each_block_config(which, M, proj, request):
         assert np.array_equal(outs[cfg], outs[0]), cfg
 
 
+@pytest.mark.parametrize("which,M", [("tiny_bf16", 5), ("tiny_bf16", 129)] +
+                         [("pi0_bf16", m) for m in (1, 16, 17, 32, 33, 50, 64, 65, 97, 128, 129, 257, 513, 1100, 1599)])
+@pytest.mark.parametrize("proj", [0, 1, 2, 3])
+def test_projection_default_path(which, M, proj, request):
+    """The default path's choice (direct few-row tiles up to one round of
+    blocks, K slices, plain tiles) at the edges of the row ranges, against
+    float64.  Bounds: bf16 outputs round once (2^-9 relative at most); fp32
+    sums of up to 4096 bf16 products."""
+    e, w = request.getfixturevalue(which)
+    sh = e.shape
+    if M > e.cap.max_action_tokens:
+        pytest.skip("above capacity")
+    layer = sh.n_layers - 1
+    rng = np.random.default_rng(70 + proj + M)
+    K_in = {0: sh.d_model, 1: sh.n_q_heads * sh.head_dim, 2: sh.d_model, 3: sh.d_mlp}[proj]
+    W = {0: w["w_qkv"], 1: w["w_o"], 2: w["w_up"], 3: w["w_down"]}[proj][layer].astype(np.float64)
+    a = bf16_round(rng.standard_normal((M, K_in)).astype(np.float32))
+    acc = a.astype(np.float64) @ W
+    a_dev = _tdev(a, "bf16")
+    if proj in (0, 2):
+        out = torch.full((M + 3, W.shape[1]), float("nan"), dtype=a_dev.dtype, device="cuda")
+        e.gemm(proj, layer, a_dev, M, out)
+        got = _thost(out)
+        assert np.isnan(got[M:]).all()                  # nothing written past the rows
+        assert rel_l2(got[:M], acc if proj == 0 else gelu_tanh(acc)) < 4e-3
+    else:
+        h0 = rng.standard_normal((M + 3, sh.d_model)).astype(np.float32)
+        gate = rng.standard_normal((M, sh.d_model)).astype(np.float32)
+        h = torch.from_numpy(h0).cuda()
+        e.gemm(proj, layer, a_dev, M, h, torch.from_numpy(gate).cuda())
+        got = h.cpu().numpy()
+        assert np.array_equal(got[M:], h0[M:])
+        assert rel_l2(got[:M].astype(np.float64) - h0[:M], gate * acc) < 1e-5
+
+
 # ------------------------------------------------------------------ attention
 
 def _attn_case(e, shapes, seed, fill_q=None, tags=None):
