@@ -198,7 +198,7 @@ void rosa_destroy(rosa_batch *b);
  *   o:   DEVICE [sum H][n_q*head_dim] in cfg's dtype, 16-byte aligned, written.
  *   hip_stream: hipStream_t the work is enqueued on (NULL = default stream).
  * The plan of the call and the partial results of key ranges split over
- * several work items live in a library-owned device array of 16.7 MiB per GPU
+ * several work items live in a library-owned device array of 16.5 MiB per GPU
  * (obtained once per device, held until the process ends): at most 1024
  * requests, 4096 attention work items and 64 split partials per call (fewer
  * key splits are made than rosa_generate_actions would make for a small

@@ -748,15 +748,17 @@ constexpr int kNaMaxRequests = 1024;
 constexpr int kNaMaxItems = 4096;          // work items, and blocks of the launch order
 constexpr int kNaMaxSlots = 64;            // partial-result slots (query blocks x key splits)
 constexpr int kNaMaxHeadDim = 256;
-constexpr size_t kNaOffReqs = 0;
-constexpr size_t kNaOffItems = kNaOffReqs + (size_t)kNaMaxRequests * sizeof(ReqDesc);
-constexpr size_t kNaOffGroups = kNaOffItems + (size_t)kNaMaxItems * sizeof(AttnItem);
-constexpr size_t kNaOffLists = kNaOffGroups + (size_t)kNaMaxSlots * sizeof(AttnGroup);
-constexpr size_t kNaOffMl = kNaOffLists + (size_t)kNaMaxItems * sizeof(AttnItem);
+// The plan's parts lie one after another (16-byte aligned) at the start of the
+// scratch, only those the launches read, so that a call uploads no more than
+// its own plan: a pageable copy of 4 KB holds the stream about 8 us, one of
+// 330 KB (every part at its largest) 27 us.  kNaPlanBytes holds the largest.
+constexpr size_t kNaPlanBytes = (size_t)kNaMaxRequests * sizeof(ReqDesc) + (size_t)kNaMaxItems * sizeof(AttnItem) +
+                                (size_t)kNaMaxSlots * sizeof(AttnGroup);
+constexpr size_t kNaOffMl = (kNaPlanBytes + 255) / 256 * 256;
 constexpr size_t kNaOffO = kNaOffMl + (size_t)kNaMaxSlots * kAttnQB * 2 * sizeof(float);
 constexpr size_t kNaBytes = kNaOffO + (size_t)kNaMaxSlots * kAttnQB * kNaMaxHeadDim * sizeof(float);
-static_assert(kNaOffItems % 256 == 0 && kNaOffGroups % 256 == 0 && kNaOffLists % 256 == 0 &&
-              kNaOffMl % 256 == 0 && kNaOffO % 256 == 0, "scratch regions stay 256-byte aligned");
+static_assert(sizeof(ReqDesc) % 16 == 0 && sizeof(AttnItem) % 16 == 0 && sizeof(AttnGroup) % 16 == 0 &&
+              kNaOffO % 256 == 0, "scratch parts stay aligned");
 }  // namespace
 
 static __device__ __align__(256) uint8_t scratch[kNaBytes];
@@ -1344,48 +1346,68 @@ rosa_status rosa_attention_noalloc(const rosa_model_config *cfg, const rosa_requ
     if (n_items > (size_t)kNaMaxItems || n_groups > (size_t)kNaMaxSlots || p.attn_lists.size() > (size_t)kNaMaxItems)
       return fail(nullptr, ROSA_E_CAPACITY, "more than 4096 attention work items or launch blocks");
 
-    // Host image of the plan regions, copied into the scratch in one transfer.
-    std::vector<uint8_t> img(kNaOffMl, 0);
-    ReqDesc *rd = reinterpret_cast<ReqDesc *>(img.data() + kNaOffReqs);
-    for (int i = 0; i < n; ++i) {
-      const rosa_request &r = reqs[p.order[i]];
-      ReqDesc d{};
-      d.pk = r.prefix_k; d.pv = r.prefix_v; d.noise = r.noise; d.actions = r.actions;
-      d.P = r.prefix_len; d.H = r.horizon; d.K = r.num_steps; d.tok_off = p.tok_off[i]; d.orig = p.order[i];
-      d.k0 = r.start_step; d.S = p.steps[i];
-      rd[i] = d;
+    const Dims D = make_dims(cfg);
+    const int v = attn_set_of(cfg, layer);
+    const Plan::AttnSet &S = p.sets[v];
+    // Host image of the plan, copied into the scratch in one transfer: this
+    // layer's launch order (bf16) or items (fp32), its merge groups, and the
+    // request descriptors where a launch reads them (the fp32 kernel, the merge).
+    const bool need_reqs = !bf16 || !S.groups.empty();
+    size_t list_lo = 0, list_n = 0;
+    if (bf16) {
+      list_lo = (size_t)p.lanes[0].list_at[v][0];
+      size_t list_hi = p.attn_lists.size();     // the next list's start (later steps', the other set's)
+      for (int v2 = 0; v2 < p.n_sets; ++v2)
+        for (int32_t at : p.lanes[0].list_at[v2])
+          if (at > (int32_t)list_lo) list_hi = std::min(list_hi, (size_t)at);
+      list_n = list_hi - list_lo;
     }
-    std::vector<AttnItem> all(S0.items);
-    all.insert(all.end(), S1.items.begin(), S1.items.end());
-    std::memcpy(img.data() + kNaOffItems, all.data(), all.size() * sizeof(AttnItem));
-    std::memcpy(img.data() + kNaOffGroups, S0.groups.data(), S0.groups.size() * sizeof(AttnGroup));
-    std::memcpy(img.data() + kNaOffGroups + S0.groups.size() * sizeof(AttnGroup), S1.groups.data(),
-                S1.groups.size() * sizeof(AttnGroup));
-    attn_order_items(all, p.attn_lists.data(), p.attn_next.data(), p.attn_lists.size(),
-                     reinterpret_cast<AttnItem *>(img.data() + kNaOffLists));
+    const size_t off_items = 0;
+    const size_t off_groups = off_items + (bf16 ? list_n : S.items.size()) * sizeof(AttnItem);
+    const size_t off_reqs = off_groups + S.groups.size() * sizeof(AttnGroup);
+    const size_t used = off_reqs + (need_reqs ? (size_t)n : 0) * sizeof(ReqDesc);
+    if (used > kNaPlanBytes) return fail(nullptr, ROSA_E_CAPACITY, "plan above the scratch size");
+    std::vector<uint8_t> img(used);
+    if (bf16) {
+      // The lists index the items of both sets, set 0's first; this layer's
+      // entries name only its own set's.
+      std::vector<int32_t> own(p.attn_lists.begin() + list_lo, p.attn_lists.begin() + list_lo + list_n);
+      for (int32_t &i : own)
+        if (i >= 0) i -= S.item_base;
+      attn_order_items(S.items, own.data(), p.attn_next.data() + list_lo, list_n,
+                       reinterpret_cast<AttnItem *>(img.data() + off_items));
+    } else {
+      std::memcpy(img.data() + off_items, S.items.data(), S.items.size() * sizeof(AttnItem));
+    }
+    std::memcpy(img.data() + off_groups, S.groups.data(), S.groups.size() * sizeof(AttnGroup));
+    if (need_reqs) {
+      ReqDesc *rd = reinterpret_cast<ReqDesc *>(img.data() + off_reqs);
+      for (int i = 0; i < n; ++i) {
+        const rosa_request &r = reqs[p.order[i]];
+        ReqDesc d{};
+        d.pk = r.prefix_k; d.pv = r.prefix_v; d.noise = r.noise; d.actions = r.actions;
+        d.P = r.prefix_len; d.H = r.horizon; d.K = r.num_steps; d.tok_off = p.tok_off[i]; d.orig = p.order[i];
+        d.k0 = r.start_step; d.S = p.steps[i];
+        rd[i] = d;
+      }
+    }
 
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     uint8_t *sp = nullptr;
     if (e == hipSuccess) e = noalloc_scratch(dev, &sp);
     const hipStream_t stream = (hipStream_t)hip_stream;
-    const size_t used = kNaOffLists + p.attn_lists.size() * sizeof(AttnItem);
     if (e == hipSuccess) e = hipMemcpyAsync(sp, img.data(), used, hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return device_fail(nullptr, e, "scratch address or plan upload");
 
-    const Dims D = make_dims(cfg);
-    const Plan::Lane &ln = p.lanes[0];
-    const int v = attn_set_of(cfg, layer);
-    const Plan::AttnSet &S = p.sets[v];
     AttnArgs a{};
-    a.items = reinterpret_cast<const AttnItem *>(sp + kNaOffItems) + S.item_base;
+    a.items = reinterpret_cast<const AttnItem *>(sp + off_items);
     a.n_items = (int)S.items.size();
     if (bf16) {
-      a.items = reinterpret_cast<const AttnItem *>(sp + kNaOffItems);
-      a.ordered = reinterpret_cast<const AttnItem *>(sp + kNaOffLists) + ln.list_at[v][0];
-      a.n_blocks = ln.list_blocks[v][0];
+      a.ordered = a.items;
+      a.n_blocks = p.lanes[0].list_blocks[v][0];
     }
-    a.reqs = reinterpret_cast<const ReqDesc *>(sp + kNaOffReqs);
+    a.reqs = reinterpret_cast<const ReqDesc *>(sp + off_reqs);
     a.layer = layer;
     a.qkv = qkv; a.ldqkv = D.qkv_dim; a.o = o; a.ldo = D.o_dim;
     a.nq = D.nq; a.nkv = D.nkv; a.hd = D.hd;
@@ -1393,7 +1415,7 @@ rosa_status rosa_attention_noalloc(const rosa_model_config *cfg, const rosa_requ
     a.part_ml = reinterpret_cast<float *>(sp + kNaOffMl);
     e = launch_attention(a, bf16, stream);
     if (e == hipSuccess && !S.groups.empty())
-      e = launch_attn_merge(reinterpret_cast<const AttnGroup *>(sp + kNaOffGroups) + S.group_base, (int)S.groups.size(),
+      e = launch_attn_merge(reinterpret_cast<const AttnGroup *>(sp + off_groups), (int)S.groups.size(),
                             a.reqs, a.part_o, a.part_ml, o, D.o_dim, D.nq, D.nkv, D.hd, bf16, stream);
     return e == hipSuccess ? ROSA_OK : device_fail(nullptr, e, "attention launch");
   } catch (const std::bad_alloc &) {

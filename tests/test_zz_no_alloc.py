@@ -101,6 +101,44 @@ def test_noalloc_attention_matches_handle_attention(dtype):
         e.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("layout", [0, 1])
+def test_noalloc_attention_uploads_its_own_plan(dtype, layout):
+    """Mixed step counts (several launch lists in the plan, of which the layer's
+    first is uploaded), both layers of either layout (in the alternating one
+    layer 1 takes the second set's list), with and without key splits."""
+    from paper_2607_01088_amd import rosa
+    shape = dataclasses.replace(SHAPE if dtype == "bf16" else TINY_SHAPE, attention_layout=layout)
+    rng = np.random.default_rng(31)
+    for n in (3, 140):
+        specs = [(int(rng.integers(1, 900)), int(rng.integers(1, 51))) for _ in range(n)]
+        keep, structs, qkv = _case(shape, dtype, specs, seed=500 + n)
+        for i, s in enumerate(structs):
+            s.num_steps = 1 + i % 5
+        qkv_h = _host(qkv)
+        nq, nkv, hd = shape.n_q_heads, shape.n_kv_heads, shape.head_dim
+        for layer in (0, 1):
+            o = torch.full((qkv.shape[0], nq * hd), float("nan"), dtype=qkv.dtype, device="cuda")
+            assert rosa.attention_noalloc(shape, dtype, structs, layer, qkv, o) == rosa.ROSA_OK, rosa.last_error_global()
+            torch.cuda.synchronize()
+            got = _host(o)
+            assert np.isfinite(got).all()
+            for i in sorted({0, 1, n // 2, n - 1}):
+                P, H = specs[i]
+                row = sum(h for _, h in specs[:i])
+                rows = qkv_h[row:row + H].astype(np.float64)
+                ka = rows[:, nq * hd:(nq + nkv) * hd].reshape(H, nkv, hd)
+                va = rows[:, (nq + nkv) * hd:].reshape(H, nkv, hd)
+                k, v = (_host(t[layer, :P]).astype(np.float64) for t in keep[i])
+                if layout == 0:
+                    k, v = np.concatenate([k, ka]), np.concatenate([v, va])
+                elif layer == 1:
+                    k, v = ka, va
+                want = oracle_attention(rows[:, : nq * hd].reshape(H, nq, hd), k, v).reshape(H, nq * hd)
+                err = rel_l2(got[row:row + H], want)
+                assert err <= (1e-2 if dtype == "bf16" else 1e-5), (n, layer, i, err)
+
+
 def test_noalloc_attention_rejects_beyond_limits():
     from paper_2607_01088_amd import rosa
     shape = SHAPE
