@@ -486,65 +486,51 @@ __global__ void __launch_bounds__(256, 2) attention_bf16_kernel(AttnArgs a) {
     const float l_all = l_run[g] + __shfl_xor(l_run[g], 32, 64);
     const int loc = 32 * (wave + 4 * g) + (lane & 31);
     if (loc >= it.nq) continue;
-    if (it.slot < 0) {
-      // Through LDS (the rings, free now): lane q writes its query row's 8-byte
-      // pieces, chunk c of a row at c ^ (q % CPRO); then rows go out as whole
-      // 16-byte chunks, consecutive lanes on consecutive chunks of a row.
-      const float inv = 1.0f / l_all;
-      uint8_t *stg = smem + (wave * NG + g) * (32 * 2 * HD);
-      const int q = lane & 31;
+    // Through LDS (the rings, free now): lane q writes its query row's 8-byte
+    // pieces, chunk c of a row at c ^ (q % CPRO); then rows go out as whole
+    // 16-byte chunks, consecutive lanes on consecutive chunks of a row.  A
+    // split item's O leaves unnormalised.
+    const float inv = it.slot < 0 ? 1.0f / l_all : 1.0f;
+    uint8_t *stg = smem + (wave * NG + g) * (32 * 2 * HD);
+    const int q = lane & 31;
 #pragma unroll
-      for (int n = 0; n < NT; ++n)
+    for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          bf16x4 v;
+      for (int rg = 0; rg < 4; ++rg) {
+        bf16x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = (bf16)(o[g][n][rg * 4 + e] * inv);
-          const int c = (4 * n + rg) ^ (q & (CPRO - 1));
-          *reinterpret_cast<bf16x4 *>(stg + q * 2 * HD + c * 16 + half * 8) = v;
-        }
+        for (int e = 0; e < 4; ++e) v[e] = (bf16)(o[g][n][rg * 4 + e] * inv);
+        const int c = (4 * n + rg) ^ (q & (CPRO - 1));
+        *reinterpret_cast<bf16x4 *>(stg + q * 2 * HD + c * 16 + half * 8) = v;
+      }
+    if (it.slot >= 0 && half == 0) {
+      float *pm = a.part_ml + ((size_t)it.slot * kAttnQB + loc) * 2;
+      pm[0] = m_ref[g] * sl2;       // log2 units, as the merge expects
+      pm[1] = l_all;
     }
   }
   __builtin_amdgcn_s_waitcnt(at::waitcnt_lgkm0);   // this wave's staging writes are done
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     const int base = 32 * (wave + 4 * g);
-    if (it.slot >= 0 || base >= it.nq) continue;
+    if (base >= it.nq) continue;
     const uint8_t *stg = smem + (wave * NG + g) * (32 * 2 * HD);
     constexpr int RPI = 64 / CPRO;          // rows per instruction
 #pragma unroll
     for (int i = 0; i < 32 / RPI; ++i) {
       const int r = i * RPI + lane / CPRO, c = lane % CPRO;
       if (base + r < it.nq) {
-        const int qrow = it.q0 + base + r;
         const uint4 v = *reinterpret_cast<const uint4 *>(stg + r * 2 * HD + ((c ^ (r & (CPRO - 1))) * 16));
-        const size_t orow = (size_t)(it.tok_off + qrow / G), ocol = (size_t)(it.kvh * G + qrow % G) * HD + c * 8;
-        // row-major, or kb32 (the 16-byte chunk stays inside one 32-wide block)
-        const size_t off = a.o_rows > 0 ? kb32_offset(a.o_rows, orow, ocol) : orow * a.ldo + ocol;
-        *reinterpret_cast<uint4 *>(reinterpret_cast<bf16 *>(a.o) + off) = v;
-      }
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    const float l_all = l_run[g] + __shfl_xor(l_run[g], 32, 64);
-    const int loc = 32 * (wave + 4 * g) + (lane & 31);
-    if (loc >= it.nq) continue;
-    if (it.slot >= 0) {
-      bf16 *po = reinterpret_cast<bf16 *>(a.part_o) + ((size_t)it.slot * kAttnQB + loc) * HD;
-#pragma unroll
-      for (int n = 0; n < NT; ++n)
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          bf16x4 v;
-#pragma unroll
-          for (int e2 = 0; e2 < 4; ++e2) v[e2] = (bf16)o[g][n][rg * 4 + e2];
-          *reinterpret_cast<bf16x4 *>(po + n * 32 + rg * 8 + half * 4) = v;
+        bf16 *dst;
+        if (it.slot >= 0) {
+          dst = reinterpret_cast<bf16 *>(a.part_o) + ((size_t)it.slot * kAttnQB + base + r) * HD + c * 8;
+        } else {
+          const int qrow = it.q0 + base + r;
+          const size_t orow = (size_t)(it.tok_off + qrow / G), ocol = (size_t)(it.kvh * G + qrow % G) * HD + c * 8;
+          // row-major, or kb32 (the 16-byte chunk stays inside one 32-wide block)
+          dst = reinterpret_cast<bf16 *>(a.o) + (a.o_rows > 0 ? kb32_offset(a.o_rows, orow, ocol) : orow * a.ldo + ocol);
         }
-      if (half == 0) {
-        float *pm = a.part_ml + ((size_t)it.slot * kAttnQB + loc) * 2;
-        pm[0] = m_ref[g] * sl2;     // log2 units, as the merge expects
-        pm[1] = l_all;
+        *reinterpret_cast<uint4 *>(dst) = v;
       }
     }
   }
