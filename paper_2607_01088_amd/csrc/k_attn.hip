@@ -70,6 +70,30 @@ struct AttnTile {
   static_assert(UNITS % 4 == 0 || UNITS < 4, "copy split");
 };
 
+// Block j of nj on XCD x reads its share of the XCD's eighth of every plane:
+// the values go nowhere, the lines stay in the XCD's L2 (and in the memory-side
+// cache for the other XCDs).
+__device__ __forceinline__ void prefetch_weights(const WeightPrefetch (&pf)[kPrefetchMats], int j, int nj, int x) {
+#pragma unroll 1
+  for (int m = 0; m < kPrefetchMats; ++m) {
+    const uint32_t per = pf[m].plane_bytes >> 7;            // 16-byte pieces of an eighth of a plane
+    const uint32_t n = per * (uint32_t)pf[m].planes;
+    const uint8_t *w = reinterpret_cast<const uint8_t *>(pf[m].w) + (size_t)x * (pf[m].plane_bytes >> 3);
+    uint32_t i = (uint32_t)j * 256 + threadIdx.x;
+    const uint32_t step = (uint32_t)nj * 256;
+    for (; i < n; i += 8 * step) {
+      uint4 v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const uint32_t e = min(i + q * step, n - 1);
+        v[q] = *reinterpret_cast<const uint4 *>(w + (size_t)(e / per) * pf[m].plane_bytes + (e % per) * 16);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) asm volatile("" ::"v"(v[q].x), "v"(v[q].y), "v"(v[q].z), "v"(v[q].w));
+    }
+  }
+}
+
 // Two blocks of four waves share a CU (two waves per SIMD): the register file
 // (at most 256 per lane) and LDS (at most 80 KB) are sized for that, and each
 // SIMD interleaves the two waves, so one wave's LDS waits and softmax work
@@ -93,6 +117,10 @@ __global__ void __launch_bounds__(256, 2) attention_bf16_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[T::LDSB];
   static_assert(T::RINGB <= 65536 + TILEB, "stage offsets must fit the LDS immediate");
 
+  if (a.n_prefetch > 0 && (int)blockIdx.x >= a.n_blocks) {
+    prefetch_weights(a.prefetch, ((int)blockIdx.x - a.n_blocks) >> 3, a.n_prefetch >> 3, blockIdx.x & 7);
+    return;
+  }
   // The block is persistent: it runs the items of its list (a.ordered[b],
   // then each entry's `next`) one after another.
   if (a.ordered[blockIdx.x].nq <= 0) return;
@@ -668,7 +696,8 @@ hipError_t launch_attention(const AttnArgs &a, bool bf16_mode, hipStream_t s) {
   if (a.o_rows > 0 && !bf16_mode) return hipErrorInvalidValue;
   if (bf16_mode) {
     if (a.n_blocks <= 0) return hipSuccess;
-    dim3 grid(a.n_blocks);
+    if (a.n_prefetch < 0 || a.n_prefetch % 8 || (a.n_prefetch > 0 && a.n_blocks % 8)) return hipErrorInvalidValue;
+    dim3 grid(a.n_blocks + a.n_prefetch);
     switch (a.hd) {
       case 32:
         if (a.causal) hipLaunchKernelGGL((attention_bf16_kernel<32, attn_groups_per_wave(32), true>), grid, dim3(256), 0, s, a);

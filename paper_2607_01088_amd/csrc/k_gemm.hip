@@ -899,7 +899,8 @@ static hipError_t launch_direct(const GemmArgs &g, hipStream_t s, bool *deferred
   if (g.K % 32 || g.N % 32 || g.a_rows < g.M) return hipErrorInvalidValue;
   const int nrt = (g.M + BM - 1) / BM, nct = (g.N + BN - 1) / BN;
   const dim3 grid((nrt * nct + 7) / 8 * 8), block(64 * KG);
-  const int strip = gemm_strip(nrt, nct, 1, BM, BN);
+  // Few rows: an XCD takes all of them for an eighth of the columns.
+  const int strip = std::max(1, (nct + 7) / 8);
   if (g.epi == kEpiGatedResidual) {
     if (g.dt) {
       hipLaunchKernelGGL((gemm_direct_kernel<MR, NC, KG, PF, kEpiGatedResidual, true>), grid, block, 0, s, g, nrt, nct, strip);

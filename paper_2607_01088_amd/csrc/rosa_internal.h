@@ -215,6 +215,11 @@ hipError_t launch_prefill_rope(const PrefillJob *jobs, const int32_t *row_job, i
 hipError_t launch_prefill_kv_scatter(const PrefillJob *jobs, const int32_t *row_job, int64_t M, const void *qkv,
                                      int ldqkv, int nq, int nkv, int hd, size_t esz, int layer, hipStream_t s);
 
+// Weights a later launch reads, to be brought into the caches by idle CUs: a
+// kb32 matrix of `planes` planes of plane_bytes bytes (a multiple of 128).
+struct WeightPrefetch { const void *w; int planes; uint32_t plane_bytes; };
+constexpr int kPrefetchMats = 4;
+
 // Attention of one layer.
 struct AttnArgs {
   const AttnItem *items; int n_items;
@@ -230,6 +235,11 @@ struct AttnArgs {
   int nq, nkv, hd;
   void *part_o;                    // [slot][kAttnQB][hd] bf16 (unnormalised O of split items)
   float *part_ml;                  // [slot][kAttnQB][2] fp32 (running max in log2 units, sum)
+  // bf16: n_prefetch more blocks (a multiple of 8, after the n_blocks) read the
+  // prefetch matrices and nothing else: block b, on XCD b % 8, its XCD's eighth of every
+  // plane, which holds the columns that XCD's blocks of a few-row launch take.
+  int n_prefetch;
+  WeightPrefetch prefetch[kPrefetchMats];
   // 1: every item's causal_b masks keys per query token (the prefix
   // producer's causal segments); such items are never key-split.
   int causal;
