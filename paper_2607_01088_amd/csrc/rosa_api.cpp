@@ -179,6 +179,13 @@ constexpr int kMinSplitKeys = kAttnMinSplitKeys;
 constexpr int kMaxSlots = kAttnMaxSlots;
 constexpr int kMaxLanes = 4;
 constexpr int kMinLaneRequests = 64;  // a batch splits into lanes only with at least this many requests per lane
+// Without a forced lane count a call of 2 kMinLaneRequests requests or more runs
+// two lanes if at least this many rows are still active three quarters through
+// its steps.  Two lanes fill each other's gaps but halve every launch: 128
+// requests of horizon 50 (6,400 rows all along) 53.6 ms in one lane, 52.3 in
+// two; 384 mixed ones (12,100 rows, half of them for half the steps) 69.1 and
+// 71.1; 256 mixed ones 48.7 and 50.9; 512 mixed ones (8,400 late rows) 100.4 and 97.6.
+constexpr int kMinLateRows = 6200;
 
 enum KernelClass {
   kcTime = 0, kcSetup, kcInProj, kcModNorm, kcGemmQKV, kcAttention, kcMerge, kcGemmO, kcGemmUp,
@@ -248,7 +255,7 @@ struct rosa_batch {
   int kb_rows = 0;
   // Lanes: sub-batches run concurrently; lane 0 uses `stream`, lane l > 0 its own
   // stream (default priority), forked after the time conditioning and joined back.
-  int lanes = 1;
+  int lanes = 0;                     // forced lane count, 0: chosen per call
   hipStream_t lane_stream[kMaxLanes] = {};
   hipEvent_t ev_fork = nullptr, ev_join[kMaxLanes] = {};
   std::string last_error;
@@ -632,6 +639,18 @@ hipError_t harvest_profile(rosa_batch *b) {
   return hipSuccess;
 }
 
+// Lanes of a call without a forced count (see kMinLateRows).  The requests are
+// not validated yet: an invalid set gets one lane and is refused by the plan.
+int auto_lanes(const rosa_request *reqs, int n, int max_steps) {
+  if (!reqs || n < 2 * kMinLaneRequests) return 1;
+  auto steps = [&](int i) { return std::min((int64_t)reqs[i].num_steps - reqs[i].start_step, (int64_t)max_steps); };
+  int64_t k_max = 0, late = 0;
+  for (int i = 0; i < n; ++i) k_max = std::max(k_max, steps(i));
+  for (int i = 0; i < n; ++i)
+    if (steps(i) > 3 * k_max / 4) late += std::max(reqs[i].horizon, 0);
+  return late >= kMinLateRows ? 2 : 1;
+}
+
 // Copy the plan through a pinned staging buffer into the device plan region.
 hipError_t upload_plan(rosa_batch *b, const Plan &p, const rosa_request *reqs, int n) {
   const Plan::AttnSet &S0 = p.sets[0], &S1 = p.sets[1];
@@ -921,7 +940,7 @@ rosa_status rosa_batch_create(const rosa_model_config *cfg, const rosa_weights *
       e = hipHostMalloc(&b->h_plan[i], b->plan_bytes, hipHostMallocDefault);
       if (e == hipSuccess) e = hipEventCreateWithFlags(&b->plan_copied[i], hipEventDisableTiming);
     }
-    b->lanes = b->bf16 ? 2 : 1;
+    b->lanes = b->bf16 ? 0 : 1;
     b->lane_stream[0] = b->stream;
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
     for (int l = 1; l < kMaxLanes && e == hipSuccess; ++l) {
@@ -982,7 +1001,8 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
     std::string err;
     // Lanes only without per-kernel profiling (its events live on one stream)
     // and with enough requests for each lane.
-    const int lanes = b->prof ? 1 : std::max(1, std::min(b->lanes, n / kMinLaneRequests));
+    const int lanes = b->prof ? 1 : std::max(1, std::min(b->lanes > 0 ? b->lanes : auto_lanes(reqs, n, max_steps),
+                                                         n / kMinLaneRequests));
     rosa_status st = build_plan(&b->cfg, &b->cap, reqs, n, true, b->bf16, lanes, p, err, max_steps);
     if (st != ROSA_OK) return fail(b, st, err);
     if (n == 0) return ROSA_OK;
