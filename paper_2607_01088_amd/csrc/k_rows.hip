@@ -41,31 +41,41 @@ hipError_t launch_setup_rows(const ReqDesc *reqs, int n_req, const int32_t *tau_
 }
 
 // h[m][n] = sum_a x[m][a] w_in[a][n] + b_in[n]   (fp32; A <= 64 is small).
-// A block covers 16 rows x 256 columns: the rows of x are staged in LDS
-// (broadcast reads) and each thread keeps its column of W_in in registers.
-constexpr int kInProjRows = 16;
+// A block covers R rows x 256 columns: the rows of x are staged in LDS and
+// read four values at a time (broadcasts), each thread keeps its column of
+// W_in (AP = 32 or 64 values, zero past A) in registers.  Few rows take blocks
+// of 4 (a block's chain is its column's loads and R rows of LDS reads: 50 rows 11 us
+// with 16 rows and one value per read), many 16, which read the weights less often.
+template <int AP, int R>
 __global__ void __launch_bounds__(256) in_proj_kernel(const float *__restrict__ x, int M, int A,
                                                       const float *__restrict__ w_in,
                                                       const float *__restrict__ b_in, int d,
                                                       float *__restrict__ h) {
-  __shared__ float xs[kInProjRows][64];
-  const int m0 = blockIdx.y * kInProjRows;
-  const int rows = min(kInProjRows, M - m0);
-  for (int i = threadIdx.x; i < kInProjRows * 64; i += 256) {
-    const int r = i / 64, a = i % 64;
+  __shared__ __attribute__((aligned(16))) float xs[R][AP];
+  const int m0 = blockIdx.y * R;
+  const int rows = min(R, M - m0);
+  const int n = blockIdx.x * 256 + threadIdx.x, nc = min(n, d - 1);
+  float w[AP];
+#pragma unroll
+  for (int a = 0; a < AP; ++a) w[a] = a < A ? w_in[(size_t)a * d + nc] : 0.f;
+  const float bias = b_in[nc];
+  for (int i = threadIdx.x; i < R * AP; i += 256) {
+    const int r = i / AP, a = i % AP;
     xs[r][a] = (r < rows && a < A) ? x[(size_t)(m0 + r) * A + a] : 0.f;
   }
   __syncthreads();
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= d) return;
-  float w[64];
-#pragma unroll
-  for (int a = 0; a < 64; ++a) w[a] = a < A ? w_in[(size_t)a * d + n] : 0.f;
-  const float bias = b_in[n];
+#pragma unroll 4
   for (int r = 0; r < rows; ++r) {
     float acc = bias;
 #pragma unroll
-    for (int a = 0; a < 64; ++a) acc = fmaf(xs[r][a], w[a], acc);
+    for (int a = 0; a < AP; a += 4) {
+      const float4 v = *reinterpret_cast<const float4 *>(&xs[r][a]);
+      acc = fmaf(v.x, w[a], acc);
+      acc = fmaf(v.y, w[a + 1], acc);
+      acc = fmaf(v.z, w[a + 2], acc);
+      acc = fmaf(v.w, w[a + 3], acc);
+    }
     h[(size_t)(m0 + r) * d + n] = acc;
   }
 }
@@ -73,8 +83,18 @@ __global__ void __launch_bounds__(256) in_proj_kernel(const float *__restrict__ 
 hipError_t launch_in_proj(const float *x, int M, int A, const float *w_in, const float *b_in, int d,
                           float *h, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  dim3 grid((d + 255) / 256, (M + kInProjRows - 1) / kInProjRows);
-  hipLaunchKernelGGL(in_proj_kernel, grid, dim3(256), 0, s, x, M, A, w_in, b_in, d, h);
+  if (A < 1 || A > 64) return hipErrorInvalidValue;
+  const int cols = (d + 255) / 256;
+  // 16 rows per block once that still gives two blocks per CU.
+  const bool many = (int64_t)cols * ((M + 15) / 16) >= 512;
+  const dim3 grid(cols, many ? (M + 15) / 16 : (M + 3) / 4);
+  if (A <= 32) {
+    if (many) hipLaunchKernelGGL((in_proj_kernel<32, 16>), grid, dim3(256), 0, s, x, M, A, w_in, b_in, d, h);
+    else hipLaunchKernelGGL((in_proj_kernel<32, 4>), grid, dim3(256), 0, s, x, M, A, w_in, b_in, d, h);
+  } else {
+    if (many) hipLaunchKernelGGL((in_proj_kernel<64, 16>), grid, dim3(256), 0, s, x, M, A, w_in, b_in, d, h);
+    else hipLaunchKernelGGL((in_proj_kernel<64, 4>), grid, dim3(256), 0, s, x, M, A, w_in, b_in, d, h);
+  }
   return hipGetLastError();
 }
 
