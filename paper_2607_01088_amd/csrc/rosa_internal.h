@@ -210,10 +210,12 @@ hipError_t launch_prefill_rope_table(float *tab, int n_pos, int head_dim, double
 // stacked QKV row (queries, then keys) at the row's position within its job.
 hipError_t launch_prefill_rope(const PrefillJob *jobs, const int32_t *row_job, int64_t M, void *qkv, int ldqkv,
                                int nheads, int head_dim, bool bf16_mode, const float *tab, hipStream_t s);
-// Layer `layer`'s K and V column blocks of the stacked QKV rows into each job's
-// caches; esz: bytes per element.
+// K and V column blocks of layers layer .. layer + n_layers - 1 of the stacked rows
+// into each job's caches; esz: bytes per element.  Layer i's K columns start nq hd
+// + i (2 nkv hd) columns into a row, its V columns after them.
 hipError_t launch_prefill_kv_scatter(const PrefillJob *jobs, const int32_t *row_job, int64_t M, const void *qkv,
-                                     int ldqkv, int nq, int nkv, int hd, size_t esz, int layer, hipStream_t s);
+                                     int ldqkv, int nq, int nkv, int hd, size_t esz, int layer, int n_layers,
+                                     hipStream_t s);
 
 // Weights a later launch reads, to be brought into the caches by idle CUs: a
 // kb32 matrix of `planes` planes of plane_bytes bytes (a multiple of 128).

@@ -497,7 +497,7 @@ rosa_status rosa_prefill_run(rosa_prefill *h, const rosa_prefix_job *jobs, int32
       if (e != hipSuccess) break;
       if (!h->context) {
         e = ptimed(h, pcScatter, [&] {
-          return launch_prefill_kv_scatter(d_jobs, d_rows, M, h->qkv, h->qkv_dim, h->nq, h->nkv, h->hd, es, l, s);
+          return launch_prefill_kv_scatter(d_jobs, d_rows, M, h->qkv, h->qkv_dim, h->nq, h->nkv, h->hd, es, l, 1, s);
         });
         // The last layer's attention and MLP feed nothing this call returns:
         // its caches are complete once its K and V are stored.
@@ -548,11 +548,10 @@ rosa_status rosa_prefill_run(rosa_prefill *h, const rosa_prefix_job *jobs, int32
       gc.a = h->u; gc.lda = h->d; gc.a_rows = h->kb_rows; gc.wt = h->wt_ctx;
       gc.M = M; gc.N = h->ctx_dim; gc.K = h->d; gc.epi = kEpiStore; gc.out = h->ctx; gc.ldo = h->ctx_dim;
       if (e == hipSuccess) e = ptimed(h, pcGemmQKV, [&] { return launch_gemm(gc, h->bf16, s, h->gemm_cfg); });
-      const size_t kv2_bytes = 2 * (size_t)h->nkv * h->hd * es;
-      for (int l = 0; l < h->head_layers && e == hipSuccess; ++l)
+      if (e == hipSuccess)
         e = ptimed(h, pcScatter, [&] {
-          return launch_prefill_kv_scatter(d_jobs, d_rows, M, (const uint8_t *)h->ctx + l * kv2_bytes, h->ctx_dim, 0,
-                                           h->nkv, h->hd, es, l, s);
+          return launch_prefill_kv_scatter(d_jobs, d_rows, M, h->ctx, h->ctx_dim, 0, h->nkv, h->hd, es, 0,
+                                           h->head_layers, s);
         });
     }
     if (e != hipSuccess) return pdevice_fail(h, e, "kernel launch");
