@@ -985,79 +985,6 @@ bool gemm_defers(const GemmArgs &g, int force_cfg, const NormArgs *then_norm) {
   return force_cfg >= 0 || gemm_choose(g, device_cu_count(), then_norm, true).ks == 1;
 }
 
-// Shift halves of deferred norms: one thread per output column of one layer's
-// product, for up to kShiftRows modulation rows at a time; the rows' shift
-// vectors pass through LDS kShiftK values of K at a time (K-major, so one
-// 16-byte read serves four rows).  Column n of a kb32 weight holds its K
-// values in 64-byte runs, one per 32 of K.
-constexpr int kShiftRows = 16, kShiftK = 256;
-__global__ void __launch_bounds__(256) shift_proj_kernel(const float *__restrict__ modtab, int mod_stride, int n_mod,
-                                                         int layer_stride, int q_off, int u_off, int d,
-                                                         const bf16 *__restrict__ wq, int Nq,
-                                                         const bf16 *__restrict__ wu, int Nu, int nbq,
-                                                         float *__restrict__ S) {
-  __shared__ __attribute__((aligned(16))) float sh[kShiftK][kShiftRows];
-  const int l = blockIdx.y, r0 = blockIdx.z * kShiftRows, nr = min(kShiftRows, n_mod - r0);
-  const bool isq = (int)blockIdx.x < nbq;
-  const int col = (isq ? (int)blockIdx.x : (int)blockIdx.x - nbq) * 256 + threadIdx.x;
-  const int N = isq ? Nq : Nu, off = isq ? q_off : u_off;
-  const bf16 *W = (isq ? wq : wu) + (size_t)l * N * d;
-  float acc[kShiftRows];
-#pragma unroll
-  for (int r = 0; r < kShiftRows; ++r) acc[r] = 0.f;
-  for (int k0 = 0; k0 < d; k0 += kShiftK) {
-    const int kn = min(kShiftK, d - k0);
-    __syncthreads();                        // the previous chunk's reads are done
-    for (int i = threadIdx.x; i < kShiftK * kShiftRows; i += 256) {
-      const int k = i / kShiftRows, r = i % kShiftRows;
-      sh[k][r] = (r < nr && k < kn) ? modtab[(size_t)(r0 + r) * mod_stride + (size_t)l * layer_stride + off + k0 + k]
-                                    : 0.f;
-    }
-    __syncthreads();
-    if (col < N) {
-      for (int kb = 0; kb < kn; kb += 32) {
-        const bf16 *wp = W + ((size_t)((k0 + kb) >> 5) * N + col) * 32;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const bf16x8 w8 = *reinterpret_cast<const bf16x8 *>(wp + 8 * c);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float w = (float)w8[e];
-            const float4 *sv = reinterpret_cast<const float4 *>(&sh[kb + 8 * c + e][0]);
-#pragma unroll
-            for (int r4 = 0; r4 < kShiftRows / 4; ++r4) {
-              const float4 v = sv[r4];
-              acc[4 * r4] = fmaf(v.x, w, acc[4 * r4]);
-              acc[4 * r4 + 1] = fmaf(v.y, w, acc[4 * r4 + 1]);
-              acc[4 * r4 + 2] = fmaf(v.z, w, acc[4 * r4 + 2]);
-              acc[4 * r4 + 3] = fmaf(v.w, w, acc[4 * r4 + 3]);
-            }
-          }
-        }
-      }
-    }
-  }
-  if (col < N) {
-    const int Nt = Nq + Nu;
-#pragma unroll
-    for (int r = 0; r < kShiftRows; ++r)
-      if (r < nr) S[((size_t)l * n_mod + r0 + r) * Nt + (isq ? 0 : Nq) + col] = acc[r];
-  }
-}
-
-hipError_t launch_shift_proj(const float *modtab, int mod_stride, int n_mod, int L, int layer_stride, int q_off,
-                             int u_off, int d, const void *wq, int Nq, const void *wu, int Nu, float *S,
-                             hipStream_t s) {
-  if (n_mod <= 0 || L <= 0) return hipSuccess;
-  if (d % 32 != 0 || Nq <= 0 || Nu <= 0) return hipErrorInvalidValue;
-  const int nbq = (Nq + 255) / 256, nbu = (Nu + 255) / 256;
-  const dim3 grid(nbq + nbu, L, (n_mod + kShiftRows - 1) / kShiftRows);
-  hipLaunchKernelGGL(shift_proj_kernel, grid, dim3(256), 0, s, modtab, mod_stride, n_mod, layer_stride, q_off, u_off,
-                     d, reinterpret_cast<const bf16 *>(wq), Nq, reinterpret_cast<const bf16 *>(wu), Nu, nbq, S);
-  return hipGetLastError();
-}
-
-
 template <int EPI>
 __device__ __forceinline__ void epilogue_f32(const GemmArgs &g, int row, int col, float v) {
   float *out = reinterpret_cast<float *>(g.out) + (size_t)row * g.ldo + col;

@@ -5,7 +5,7 @@
 // distinct tau and looked up per row afterwards.  The weights of this stage
 // (two d x d time-MLP matrices and L+1 modulation projections, about 0.23 GB in
 // bf16 for the pi0 shape) are streamed once per call for all distinct taus
-// together: the kernel is HBM-bound on weight bytes.
+// together: the kernels are HBM-bound on weight bytes.
 #include <algorithm>
 
 #include "rosa_device.h"
@@ -34,8 +34,8 @@ hipError_t launch_time_embedding(const float *taus, int n_tau, int dt, float *em
 }
 
 // Y[t][col] = act(sum_k X[t][k] W[k][col] + b[col]) for up to 16 rows t per
-// pass.  A thread owns two adjacent columns: the wave reads 256 contiguous
-// bytes of a weight row per k (bf16) and uses each weight for all rows.  X
+// pass (fp32 mode).  A thread owns two adjacent columns and uses each weight
+// for all rows.  X
 // is staged in LDS transposed ([k][t]), so the 16 row values of one k are four
 // broadcast 16-byte LDS reads.  The kernel is bound by streaming W once; to
 // keep enough bytes in flight each thread issues 16 weight loads at a time
@@ -43,9 +43,8 @@ hipError_t launch_time_embedding(const float *taus, int n_tau, int dt, float *em
 // slice order by small_gemv_reduce_kernel (deterministic).
 constexpr int kGemvChunk = 128;
 constexpr int kGemvRows = 16;
-template <typename WT>
 __global__ void __launch_bounds__(256) small_gemv_kernel(const float *__restrict__ X, int n, int K,
-                                                         const WT *__restrict__ W, int N,
+                                                         const float *__restrict__ W, int N,
                                                          int k_per_slice, float *__restrict__ P) {
   constexpr int NT = kGemvRows;
   __shared__ __attribute__((aligned(16))) float xs[kGemvChunk][NT];
@@ -54,7 +53,7 @@ __global__ void __launch_bounds__(256) small_gemv_kernel(const float *__restrict
   float acc0[NT], acc1[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc0[t] = acc1[t] = 0.f;
-  const WT *Wp = W + min(col, N - 2);
+  const float *Wp = W + min(col, N - 2);
   for (int k0 = kb; k0 < ke; k0 += kGemvChunk) {
     const int kn = min(kGemvChunk, ke - k0);
     __syncthreads();
@@ -68,15 +67,9 @@ __global__ void __launch_bounds__(256) small_gemv_kernel(const float *__restrict
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const int kk = min(kk0 + u, kn - 1);
-        if constexpr (sizeof(WT) == 2) {
-          const uint32_t v = *reinterpret_cast<const uint32_t *>(Wp + (size_t)(k0 + kk) * N);
-          w0[u] = __uint_as_float(v << 16);
-          w1[u] = __uint_as_float(v & 0xffff0000u);
-        } else {
-          const float2 f = *reinterpret_cast<const float2 *>(Wp + (size_t)(k0 + kk) * N);
-          w0[u] = f.x;
-          w1[u] = f.y;
-        }
+        const float2 f = *reinterpret_cast<const float2 *>(Wp + (size_t)(k0 + kk) * N);
+        w0[u] = f.x;
+        w1[u] = f.y;
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
@@ -119,8 +112,8 @@ __global__ void small_gemv_reduce_kernel(const float *__restrict__ P, int slices
 
 size_t small_gemv_workspace_floats(int N) { return (size_t)kGemvMaxSlices * kGemvRows * N; }
 
-hipError_t launch_small_gemv(const float *X, int n, int K, const void *W, bool w_bf16, const float *b,
-                             int N, int act, float *Y, float *ws, hipStream_t s) {
+hipError_t launch_small_gemv(const float *X, int n, int K, const float *W, const float *b, int N, int act, float *Y,
+                             float *ws, hipStream_t s) {
   if (N % 2) return hipErrorInvalidValue;
   for (int t0 = 0; t0 < n; t0 += kGemvRows) {
     const int nt = std::min(kGemvRows, n - t0);
@@ -130,12 +123,7 @@ hipError_t launch_small_gemv(const float *X, int n, int K, const void *W, bool w
     const int kps = ((K + want - 1) / want + kGemvChunk - 1) / kGemvChunk * kGemvChunk;
     const int slices = (K + kps - 1) / kps;
     dim3 grid(cols, 1, slices);
-    if (w_bf16)
-      hipLaunchKernelGGL(small_gemv_kernel<bf16>, grid, dim3(256), 0, s, X + (size_t)t0 * K, nt, K,
-                         (const bf16 *)W, N, kps, ws);
-    else
-      hipLaunchKernelGGL(small_gemv_kernel<float>, grid, dim3(256), 0, s, X + (size_t)t0 * K, nt, K,
-                         (const float *)W, N, kps, ws);
+    hipLaunchKernelGGL(small_gemv_kernel, grid, dim3(256), 0, s, X + (size_t)t0 * K, nt, K, W, N, kps, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t total = (size_t)nt * N;
@@ -145,6 +133,152 @@ hipError_t launch_small_gemv(const float *X, int n, int K, const void *W, bool w
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// ------------------------------------------------------------------ bf16 weights
+// Y[t][col] = act(sum_k X[t][k] W[k][col] + b[col]) for up to 16 rows t of fp32 X
+// and bf16 W (kb32, K padded to 32), on the matrix cores without giving up
+// fp32 inputs: X = hi + mid + lo in bf16, each the rounded remainder of
+// the ones before (24 bits and more together), so three
+// v_mfma_f32_16x16x32_bf16 per weight fragment form the exact products and
+// accumulate them in fp32.  The eight waves split K; a wave keeps its share of X
+// (up to 128 of K) in registers and streams weights: CT tiles of 16 columns per
+// step, every load of the next step in flight while the waves' partial sums meet in
+// LDS and are added in wave order.  Bound by streaming W once: the 0.23 GB
+// modulation weights take 50 us (a kernel on the vector units took 79 and a reduction
+// launch), a 2 MB time-MLP matrix 6 us (28).
+constexpr int kTauRows = 16, kTauWaves = 8, kTauSteps = 4;
+template <int CT>
+__global__ void __launch_bounds__(64 * kTauWaves) tau_gemm_kernel(const float *__restrict__ X, int ldx, size_t x_stride,
+                                                                  int n_rows, int K, const bf16 *__restrict__ W,
+                                                                  size_t w_stride, int N, const float *__restrict__ b,
+                                                                  int act, float *__restrict__ Y, int ldy,
+                                                                  size_t y_stride, int vec) {
+  constexpr int LDR = 20;                   // floats per staged row of 16 (padded)
+  __shared__ __attribute__((aligned(16))) float red[2][kTauWaves][CT][16 * LDR];
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t0 = blockIdx.z * kTauRows, n = min(kTauRows, n_rows - t0);
+  X += blockIdx.y * x_stride + (size_t)t0 * ldx;
+  W += blockIdx.y * w_stride;
+  Y += blockIdx.y * y_stride + (size_t)t0 * ldy;
+  const int T = (K + 31) >> 5;              // steps of 32 of K, in chunks of 8 kTauSteps
+  const int n_chunks = (T + kTauWaves * kTauSteps - 1) / (kTauWaves * kTauSteps);
+  auto share = [&](int c, int &lo, int &cnt) __attribute__((always_inline)) {
+    const int s0 = c * kTauWaves * kTauSteps, tc = min(kTauWaves * kTauSteps, T - s0);
+    lo = s0 + tc * wave / kTauWaves;
+    cnt = s0 + tc * (wave + 1) / kTauWaves - lo;
+  };
+  // Lane holds row lane % 16, K values 8 (lane / 16) .. + 7 of each step.
+  bf16x8 xh[kTauSteps], xm[kTauSteps], xl[kTauSteps];
+  auto load_x = [&](int lo, int cnt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < kTauSteps; ++s) {
+      float v[8];
+      const int k = (lo + s) * 32 + 8 * q4;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = (s < cnt && r16 < n && k + j < K) ? X[(size_t)r16 * ldx + k + j] : 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const bf16 h = (bf16)v[j];
+        const float r1 = v[j] - (float)h;
+        const bf16 m = (bf16)r1;
+        xh[s][j] = h;
+        xm[s][j] = m;
+        xl[s][j] = (bf16)(r1 - (float)m);
+      }
+    }
+  };
+  bf16x8 wv[kTauSteps][CT];
+  auto load_w = [&](int g, int lo, int cnt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < kTauSteps; ++s)
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+        if (s < cnt) {
+          const int col = min((g * CT + c) * 16, N - 16) + r16;
+          wv[s][c] = *reinterpret_cast<const bf16x8 *>(W + ((size_t)(lo + s) * N + col) * 32 + 8 * q4);
+        }
+  };
+  const int n_groups = (N / 16 + CT - 1) / CT;
+  int lo, cnt;
+  share(0, lo, cnt);
+  int g = blockIdx.x;
+  if (g < n_groups) load_w(g, lo, cnt);
+  load_x(lo, cnt);
+  for (int it = 0; g < n_groups; ++it, g += gridDim.x) {
+    f32x4 acc[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int ch = 0; ch < n_chunks; ++ch) {
+      if (n_chunks > 1) {                   // the share of X changes with the chunk
+        share(ch, lo, cnt);
+        load_w(g, lo, cnt);
+        load_x(lo, cnt);
+      }
+#pragma unroll
+      for (int s = 0; s < kTauSteps; ++s)
+        if (s < cnt) {
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[s][c], xl[s], acc[c], 0, 0, 0);
+            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[s][c], xm[s], acc[c], 0, 0, 0);
+            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[s][c], xh[s], acc[c], 0, 0, 0);
+          }
+        }
+    }
+    if (n_chunks == 1 && g + (int)gridDim.x < n_groups) load_w(g + gridDim.x, lo, cnt);
+    // Lane holds row (t) lane % 16, columns 4 (lane / 16) .. + 3 of each tile.  Two
+    // staging buffers: a buffer is written again only after the other's barrier.
+    float(*rb)[CT][16 * LDR] = red[it & 1];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) *reinterpret_cast<f32x4 *>(&rb[wave][c][r16 * LDR + 4 * q4]) = acc[c];
+    __syncthreads();
+    if (tid < CT * 64) {
+      const int c = tid >> 6, t = (tid & 63) >> 2, c4 = (tid & 3) * 4, col = (g * CT + c) * 16 + c4;
+      f32x4 v = *reinterpret_cast<const f32x4 *>(&rb[0][c][t * LDR + c4]);
+#pragma unroll
+      for (int w = 1; w < kTauWaves; ++w) {
+        const f32x4 p = *reinterpret_cast<const f32x4 *>(&rb[w][c][t * LDR + c4]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] += p[k];
+      }
+      if (t < n && col < N) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (b) v[k] += b[col + k];
+          if (act == 1) v[k] = silu_f(v[k]);
+        }
+        float *y = Y + (size_t)t * ldy + col;
+        if (vec) {
+          *reinterpret_cast<f32x4 *>(y) = v;
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) y[k] = v[k];
+        }
+      }
+    }
+  }
+}
+
+hipError_t launch_tau_gemm(const float *X, int ldx, size_t x_stride, int n, int K, const void *W, size_t w_stride, int N,
+                           const float *b, int act, float *Y, int ldy, size_t y_stride, int n_mat, hipStream_t s) {
+  if (n <= 0 || n_mat <= 0) return hipSuccess;
+  if (K < 1 || N < 16 || N % 16) return hipErrorInvalidValue;
+  const int vec = ldy % 4 == 0 && y_stride % 4 == 0 && ((uintptr_t)Y & 15) == 0;   // 16-byte stores
+  const int chunks = (n + kTauRows - 1) / kTauRows;
+  // Wide matrices 64 columns per step over at most 256 persistent blocks (two
+  // steps each when many matrices share the launch); narrow ones 16 per block.
+  if (N >= 2048) {
+    const int groups = (N + 63) / 64;
+    const int blocks = n_mat > 1 ? (groups + 1) / 2 : std::min(groups, 256);
+    hipLaunchKernelGGL(tau_gemm_kernel<4>, dim3(blocks, n_mat, chunks), dim3(64 * kTauWaves), 0, s, X, ldx, x_stride, n, K,
+                       (const bf16 *)W, w_stride, N, b, act, Y, ldy, y_stride, vec);
+  } else {
+    hipLaunchKernelGGL(tau_gemm_kernel<1>, dim3(N / 16, n_mat, chunks), dim3(64 * kTauWaves), 0, s, X, ldx, x_stride, n, K,
+                       (const bf16 *)W, w_stride, N, b, act, Y, ldy, y_stride, vec);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace rosa

@@ -132,18 +132,22 @@ uint16_t f32_to_bf16_rne(float f) {
 }
 
 hipError_t upload_weights_kb32(void *dst, const float *src, int L, int K, int N) {
-  const size_t per = (size_t)K * N;
+  const int planes = (K + 31) / 32;
+  const size_t per = (size_t)planes * 32 * N;
   std::vector<uint16_t> tmp(per * L);
-  auto work = [&](int l) {
-    const float *s = src + per * l;
-    uint16_t *d = tmp.data() + per * l;
-    for (int k = 0; k < K; ++k)
-      for (int n = 0; n < N; ++n) d[kb32_offset(N, n, k)] = f32_to_bf16_rne(s[(size_t)k * N + n]);
+  // One 32-wide plane of one matrix, 64 columns at a time (8 KB read, 4 KB written).
+  auto work = [&](int l, int kb) {
+    const float *s = src + ((size_t)l * K + (size_t)kb * 32) * N;
+    uint16_t *d = tmp.data() + per * l + (size_t)kb * 32 * N;
+    const int kn = std::min(32, K - kb * 32);
+    for (int n0 = 0; n0 < N; n0 += 64)
+      for (int k = 0; k < kn; ++k)
+        for (int n = n0; n < std::min(N, n0 + 64); ++n) d[(size_t)n * 32 + k] = f32_to_bf16_rne(s[(size_t)k * N + n]);
   };
   std::vector<std::thread> th;
-  const int nt = std::max(1, std::min(L, 8));
+  const int units = L * planes, nt = std::max(1, std::min(units, 8));
   for (int t = 0; t < nt; ++t)
-    th.emplace_back([&, t] { for (int l = t; l < L; l += nt) work(l); });
+    th.emplace_back([&, t] { for (int u = t; u < units; u += nt) work(u / planes, u % planes); });
   for (auto &x : th) x.join();
   return hipMemcpy(dst, tmp.data(), tmp.size() * 2, hipMemcpyHostToDevice);
 }
@@ -590,12 +594,10 @@ T *dalloc(rosa_batch *b, size_t count, hipError_t &e) {
   return (T *)ptr;
 }
 
-// Upload a host fp32 tensor, converted to the activation dtype.
-hipError_t upload_act(rosa_batch *b, void *dst, const float *src, size_t n) {
-  if (!b->bf16) return hipMemcpy(dst, src, n * 4, hipMemcpyHostToDevice);
-  std::vector<uint16_t> tmp(n);
-  for (size_t i = 0; i < n; ++i) tmp[i] = f32_to_bf16_rne(src[i]);
-  return hipMemcpy(dst, tmp.data(), n * 2, hipMemcpyHostToDevice);
+// Upload a time-conditioning weight [K][N] in the layout of the mode's kernel.
+hipError_t upload_tau_weights(rosa_batch *b, void *dst, const float *src, int K, int N) {
+  if (b->bf16) return upload_weights_kb32(dst, src, 1, K, N);
+  return hipMemcpy(dst, src, (size_t)K * N * 4, hipMemcpyHostToDevice);
 }
 
 // Upload L stacked [K][N] matrices as [L][N][K] (transposed), activation dtype.
@@ -697,12 +699,16 @@ hipError_t upload_plan(rosa_batch *b, const Plan &p, const rosa_request *reqs, i
 hipError_t run_time_conditioning(rosa_batch *b, const float *d_taus, int n_tau, float *out) {
   const Dims &D = b->dims;
   hipError_t e = timed(b, kcTime, [&] { return launch_time_embedding(d_taus, n_tau, D.dt, b->emb, b->stream); });
-  if (e == hipSuccess)
-    e = timed(b, kcTime, [&] { return launch_small_gemv(b->emb, n_tau, D.dt, b->w_t1, b->bf16, b->b_t1, D.d, 1, b->tc1, b->gemv_ws, b->stream); });
-  if (e == hipSuccess)
-    e = timed(b, kcTime, [&] { return launch_small_gemv(b->tc1, n_tau, D.d, b->w_t2, b->bf16, b->b_t2, D.d, 1, b->tc2, b->gemv_ws, b->stream); });
-  if (e == hipSuccess)
-    e = timed(b, kcTime, [&] { return launch_small_gemv(b->tc2, n_tau, D.d, b->w_modall, b->bf16, b->b_modall, D.mod_stride, 0, out, b->gemv_ws, b->stream); });
+  auto product = [&](const float *x, int K, const void *w, const float *bias, int N, int act, float *y) {
+    if (e == hipSuccess)
+      e = timed(b, kcTime, [&] {
+        return b->bf16 ? launch_tau_gemm(x, K, 0, n_tau, K, w, 0, N, bias, act, y, N, 0, 1, b->stream)
+                       : launch_small_gemv(x, n_tau, K, (const float *)w, bias, N, act, y, b->gemv_ws, b->stream);
+      });
+  };
+  product(b->emb, D.dt, b->w_t1, b->b_t1, D.d, 1, b->tc1);
+  product(b->tc1, D.d, b->w_t2, b->b_t2, D.d, 1, b->tc2);
+  product(b->tc2, D.d, b->w_modall, b->b_modall, D.mod_stride, 0, out);
   return e;
 }
 
@@ -873,7 +879,9 @@ rosa_status rosa_batch_create(const rosa_model_config *cfg, const rosa_weights *
     // weights
     b->w_in = dalloc<float>(b, (size_t)D.A * d, e);
     b->b_in = dalloc<float>(b, d, e);
-    b->w_t1 = dalloc<uint8_t>(b, (size_t)D.dt * d * b->esz, e);
+    // The time-conditioning weights: row-major [K][N] in fp32 mode, kb32 (K padded
+    // to 32) in bf16 mode.
+    b->w_t1 = dalloc<uint8_t>(b, (size_t)(D.dt + 31) / 32 * 32 * d * b->esz, e);
     b->b_t1 = dalloc<float>(b, d, e);
     b->w_t2 = dalloc<uint8_t>(b, d * d * b->esz, e);
     b->b_t2 = dalloc<float>(b, d, e);
@@ -901,7 +909,7 @@ rosa_status rosa_batch_create(const rosa_model_config *cfg, const rosa_weights *
     b->emb = dalloc<float>(b, (size_t)kMaxTau * D.dt, e);
     b->tc1 = dalloc<float>(b, (size_t)kMaxTau * d, e);
     b->tc2 = dalloc<float>(b, (size_t)kMaxTau * d, e);
-    b->gemv_ws = dalloc<float>(b, small_gemv_workspace_floats(std::max(D.mod_stride, D.d)), e);
+    if (!b->bf16) b->gemv_ws = dalloc<float>(b, small_gemv_workspace_floats(std::max(D.mod_stride, D.d)), e);
     const int n_sets = cfg->attention_layout == ROSA_ATTN_ALTERNATING ? 2 : 1;
     b->max_slots = n_sets * kMaxSlots;
     b->gemm_part_floats = b->bf16 ? std::min<size_t>((size_t)kSplitMax * maxM * std::max(D.qkv_dim, std::max(D.dff, D.d)),
@@ -960,11 +968,11 @@ rosa_status rosa_batch_create(const rosa_model_config *cfg, const rosa_weights *
     std::memcpy(bmodall.data() + L * 6 * d, w->b_fmod, 2 * d * 4);
     if (e == hipSuccess) e = hipMemcpy(b->w_in, w->w_in, (size_t)D.A * d * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->b_in, w->b_in, d * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = upload_act(b, b->w_t1, w->w_t1, (size_t)D.dt * d);
+    if (e == hipSuccess) e = upload_tau_weights(b, b->w_t1, w->w_t1, D.dt, D.d);
     if (e == hipSuccess) e = hipMemcpy(b->b_t1, w->b_t1, d * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = upload_act(b, b->w_t2, w->w_t2, d * d);
+    if (e == hipSuccess) e = upload_tau_weights(b, b->w_t2, w->w_t2, D.d, D.d);
     if (e == hipSuccess) e = hipMemcpy(b->b_t2, w->b_t2, d * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = upload_act(b, b->w_modall, modall.data(), modall.size());
+    if (e == hipSuccess) e = upload_tau_weights(b, b->w_modall, modall.data(), D.d, D.mod_stride);
     if (e == hipSuccess) e = hipMemcpy(b->b_modall, bmodall.data(), bmodall.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = upload_gemm_weights(b->wt_qkv, w->w_qkv, D.L, D.d, D.qkv_dim, b->bf16);
     if (e == hipSuccess) e = upload_gemm_weights(b->wt_o, w->w_o, D.L, D.o_dim, D.d, b->bf16);
@@ -1046,10 +1054,16 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
         }
     }
     const int n_dn = D.qkv_dim + D.dff;
+    // Layer l's rows: its attention norm's shift times W_qkv, its MLP norm's times
+    // W_up, per modulation row [qkv_dim | dff].
     if (e == hipSuccess && defer_on)
       e = timed(b, kcTime, [&] {
-        return launch_shift_proj(b->modtab, D.mod_stride, n_tau, D.L, 6 * D.d, 0, 3 * D.d, D.d, b->wt_qkv, D.qkv_dim,
-                                 b->wt_up, D.dff, b->dn_shift, b->stream);
+        const size_t ys = (size_t)n_tau * n_dn, xs = (size_t)6 * D.d;
+        const hipError_t e1 = launch_tau_gemm(b->modtab, D.mod_stride, xs, n_tau, D.d, b->wt_qkv, (size_t)D.qkv_dim * D.d,
+                                              D.qkv_dim, nullptr, 0, b->dn_shift, n_dn, ys, D.L, b->stream);
+        if (e1 != hipSuccess) return e1;
+        return launch_tau_gemm(b->modtab + 3 * D.d, D.mod_stride, xs, n_tau, D.d, b->wt_up, (size_t)D.dff * D.d, D.dff,
+                               nullptr, 0, b->dn_shift + D.qkv_dim, n_dn, ys, D.L, b->stream);
       });
     // Fork: every other lane's stream waits for the plan, the modulation table
     // and the row setup.

@@ -98,12 +98,18 @@ static_assert(sizeof(PrefillJob) == 32, "PrefillJob is 32 bytes");
 
 // Time conditioning.
 hipError_t launch_time_embedding(const float *taus, int n_tau, int dt, float *emb, hipStream_t s);
-// Y[n][N] = act(X[n][K] W[K][N] + b); act: 0 none, 1 SiLU.  W row-major [K][N].
-// ws: workspace of small_gemv_workspace_floats(N) floats (K-slice partials).
+// fp32 mode: Y[n][N] = act(X[n][K] W[K][N] + b); act: 0 none, 1 SiLU.  W row-major
+// [K][N].  ws: workspace of small_gemv_workspace_floats(N) floats (K-slice partials).
 constexpr int kGemvMaxSlices = 8;
 size_t small_gemv_workspace_floats(int N);
-hipError_t launch_small_gemv(const float *X, int n, int K, const void *W, bool w_bf16, const float *b,
-                             int N, int act, float *Y, float *ws, hipStream_t s);
+hipError_t launch_small_gemv(const float *X, int n, int K, const float *W, const float *b, int N, int act, float *Y,
+                             float *ws, hipStream_t s);
+// bf16 mode, fp32 X (row stride ldx) and Y (ldy): the same for n_mat
+// matrices, matrix i at W + i w_stride elements (kb32 [ceil(K/32)][N][32], zero
+// past K; N a multiple of 16), its X and Y x_stride and y_stride floats further.
+// b (one matrix only) may be NULL.  The products are exact, the sums fp32.
+hipError_t launch_tau_gemm(const float *X, int ldx, size_t x_stride, int n, int K, const void *W, size_t w_stride, int N,
+                           const float *b, int act, float *Y, int ldy, size_t y_stride, int n_mat, hipStream_t s);
 
 // Row kernels.
 hipError_t launch_setup_rows(const ReqDesc *reqs, int n_req, const int32_t *tau_idx, int max_steps,
@@ -186,14 +192,6 @@ constexpr int kFusedNormMax = 2048;
 hipError_t launch_gemm(const GemmArgs &g, bool bf16, hipStream_t s, int force_cfg = -1,
                        const NormArgs *then_norm = nullptr, bool *normed = nullptr, bool *deferred = nullptr);
 bool gemm_defers(const GemmArgs &g, int force_cfg, const NormArgs *then_norm);
-// The shift halves of a deferred norm's products: for layer l < L, modulation
-// row r < n_mod and column n, S[(l * n_mod + r) * (Nq + Nu) + n] = sum_k
-// modtab[r * mod_stride + l * layer_stride + q_off + k] * Wq_l[k][n] for n < Nq,
-// and the same with u_off and Wu_l for the Nu columns after them (Wq, Wu:
-// bf16 kb32 [K/32][N][32] per layer, K = d).
-hipError_t launch_shift_proj(const float *modtab, int mod_stride, int n_mod, int L, int layer_stride, int q_off,
-                             int u_off, int d, const void *wq, int Nq, const void *wu, int Nu, float *S,
-                             hipStream_t s);
 // Block configurations of the bf16 GEMM (tiles from 384 x 128 down to 64 x 32).
 // A forced configuration never splits K, so every one computes each output
 // with the same instruction sequence.
@@ -259,8 +257,8 @@ uint16_t f32_to_bf16_rne(float f);
 // Host: upload L stacked [K][N] fp32 matrices as [L][N][K] (K contiguous), in
 // bf16 or fp32; synchronous.
 hipError_t upload_weights_transposed(void *dst, const float *src, int L, int K, int N, bool bf16);
-// Host: the projection weights of the bf16 GEMM: L stacked [K][N] fp32
-// matrices as bf16 kb32 [L][K/32][N][32]; synchronous.
+// Host: weights of the bf16 kernels: L stacked [K][N] fp32 matrices as bf16 kb32
+// [L][ceil(K/32)][N][32], zero past K; synchronous.
 hipError_t upload_weights_kb32(void *dst, const float *src, int L, int K, int N);
 // The projection weights in the form launch_gemm expects for the mode.
 inline hipError_t upload_gemm_weights(void *dst, const float *src, int L, int K, int N, bool bf16) {

@@ -90,6 +90,38 @@ def test_time_conditioning_matches_oracle(which, request):
         assert rel_l2(got[i], ref) < 1e-5, (tau, rel_l2(got[i], ref))
 
 
+@pytest.mark.parametrize("d,dt,n", [(128, 30, 1), (128, 8, 15), (256, 128, 16), (384, 96, 17), (1152, 2050, 33), (2176, 1024, 128)])
+def test_time_conditioning_bf16_shapes(d, dt, n):
+    """The bf16 path's products with fp32 inputs: widths that are no multiple of
+    32 (the padded K), one and several chunks of K and of flow times, narrow and
+    wide outputs, an output that is only 4-byte aligned; against the oracle
+    within fp32 rounding of sums of up to 2176 products."""
+    from synthetic import ModelShape, make_weights
+    from paper_2607_01088_amd import rosa
+    sh = ModelShape(n_layers=1, d_model=d, n_q_heads=4, n_kv_heads=1, head_dim=32, d_mlp=128, action_dim=7, time_emb_dim=dt)
+    w = make_weights(sh, "bf16", seed=5)
+    rng = np.random.default_rng(6)
+    for k in ("b_t1", "b_t2", "b_mod", "b_fmod"):
+        w[k] = rng.standard_normal(w[k].shape).astype(np.float32)
+    e = rosa.ActionExpert(sh, "bf16", w, rosa.capacity(1, 4, 4, 4, 4))
+    try:
+        taus = [float(np.float32(i) / np.float32(n)) for i in range(n)]
+        stride = 6 * d + 2 * d
+        buf = torch.full((n * stride + 2,), float("nan"), dtype=torch.float32, device="cuda")
+        out = buf[1:1 + n * stride].view(n, stride)
+        e.time_conditioning(taus, out)
+        got = buf.cpu().numpy()
+        assert np.isnan(got[0]) and np.isnan(got[-1])
+        got = got[1:-1].reshape(n, stride)
+        om = OracleModel(w, sh)
+        for i in sorted({0, n // 2, n - 1}):
+            s = om.time_condition(taus[i])
+            ref = np.concatenate([np.concatenate(om.block_modulation(s, 0)), np.concatenate(om.final_modulation(s))])
+            assert rel_l2(got[i], ref) < 1e-5, (i, rel_l2(got[i], ref))
+    finally:
+        e.close()
+
+
 # ------------------------------------------------------------------ projections
 
 @pytest.mark.parametrize("which", ["tiny_fp32", "tiny_bf16", "pi0_bf16"])
