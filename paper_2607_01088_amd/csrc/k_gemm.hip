@@ -240,9 +240,45 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs &g, int m0, int n0,
 // which must be free (gemm_mainloop ends that way).  DN: the deferred norm's
 // part of the epilogue (outputs t and the row sums of squares after a gated
 // residual; the norm's completion before a bf16 store).
+// 1 / rms and modulation row of this lane's row in each of its 32-row blocks,
+// for the completion of a deferred norm.
+template <typename T>
+struct NormRows { float rinv[T::MBW]; int mrow[T::MBW]; };
+
+// The rows' sums of squares are summed over the two lane halves (each half sums
+// its share of the row's block sums in order; the halves' totals are then added).
+// Called before the main loop, whose first copies cover these loads.
+template <typename T>
+__device__ __forceinline__ void gemm_norm_rows(const GemmArgs &g, int m0, NormRows<T> &nr) {
+  constexpr int MBW = T::MBW;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % T::NW;
+  const int wm = wave / T::WN, r32 = lane & 31, half = lane >> 5;
+  // Every load is issued before the first sum (cparts = 8 nv, nv <= 4).
+  const int nv = g.cparts >> 3;
+  f32x4 pv[MBW][4];
+#pragma unroll
+  for (int i = 0; i < MBW; ++i) {
+    const int row = min(m0 + (wm * MBW + i) * 32 + r32, g.M - 1);
+    const f32x4 *sp = reinterpret_cast<const f32x4 *>(g.css + (size_t)row * g.cparts) + half * nv;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (v < nv) pv[i][v] = sp[v];
+    nr.mrow[i] = g.rowmod[row];
+  }
+#pragma unroll
+  for (int i = 0; i < MBW; ++i) {
+    float ss = 0.f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (v < nv) ss = (((ss + pv[i][v][0]) + pv[i][v][1]) + pv[i][v][2]) + pv[i][v][3];
+    ss += __shfl_xor(ss, 32, 64);
+    nr.rinv[i] = 1.0f / sqrtf(ss / (float)g.cd + g.ceps);
+  }
+}
+
 template <typename T, int EPI, bool DN = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int m0, int n0, uint8_t *L,
-                                              f32x16 (&acc)[T::MBW][T::TN]) {
+                                              f32x16 (&acc)[T::MBW][T::TN], const NormRows<T> &nr) {
   constexpr int MBW = T::MBW, TN = T::TN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % T::NW;
@@ -369,69 +405,39 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int m0, int n0,
     // Each wave stages one 32 x 32 tile at a time in its own 4 KB slot, then
     // reads it back row-contiguous.
     uint8_t *stg = L + wave * 4096;
-    // Deferred norm: 1 / rms of this lane's row in each row block, its sum of
-    // squares taken over the two lane halves (each half sums its share of the
-    // row's block sums in order; the halves' totals are then added).
-    // The shift rows of every column this lane stores are loaded here too, all
-    // before the first store (the stores could alias them for the compiler);
-    // 16-wave tiles (no registers to spare) load each 32 x 32 tile's before it.
-    constexpr bool kShAll = DN && T::NW < 16;
-    float rinv[DN ? MBW : 1];
-    int mrow[DN ? MBW : 1];
-    f32x4 shv[kShAll ? MBW : 1][kShAll ? TN : 1][4];
-    auto load_shift = [&](int i, int j, f32x4 (&dst)[4]) __attribute__((always_inline)) {
-      const float *shrow = g.cshift + (size_t)mrow[i] * g.cshift_stride;
+    // Deferred norm: the shift rows of a 32 x 32 tile's columns, requested one
+    // tile ahead (the first before the others' LDS staging starts).
+    constexpr int Q = MBW * TN;
+    f32x4 sh[DN ? 2 : 1][4];
+    auto load_shift = [&](int q, f32x4 (&dst)[4]) __attribute__((always_inline)) {
+      const float *shrow = g.cshift + (size_t)nr.mrow[q / TN] * g.cshift_stride;
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
-        const int c4 = n0 + (wn * TN + j) * 32 + 8 * gq + 4 * half;
+        const int c4 = n0 + (wn * TN + q % TN) * 32 + 8 * gq + 4 * half;
         dst[gq] = c4 < g.N ? *reinterpret_cast<const f32x4 *>(shrow + c4) : f32x4{0.f, 0.f, 0.f, 0.f};
       }
     };
-    if constexpr (DN) {
-      // Every load is issued before the first sum (cparts = 8 nv, nv <= 4).
-      const int nv = g.cparts >> 3;
-      f32x4 pv[MBW][4];
-#pragma unroll
-      for (int i = 0; i < MBW; ++i) {
-        const int row = min(m0 + (wm * MBW + i) * 32 + r32, g.M - 1);
-        const f32x4 *sp = reinterpret_cast<const f32x4 *>(g.css + (size_t)row * g.cparts) + half * nv;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (v < nv) pv[i][v] = sp[v];
-        mrow[i] = g.rowmod[row];
-        if constexpr (kShAll) {
-#pragma unroll
-          for (int j = 0; j < TN; ++j) load_shift(i, j, shv[i][j]);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < MBW; ++i) {
-        float ss = 0.f;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (v < nv) ss = (((ss + pv[i][v][0]) + pv[i][v][1]) + pv[i][v][2]) + pv[i][v][3];
-        ss += __shfl_xor(ss, 32, 64);
-        rinv[i] = 1.0f / sqrtf(ss / (float)g.cd + g.ceps);
-      }
-    }
+    if constexpr (DN) load_shift(0, sh[0]);
 #pragma unroll
     for (int i = 0; i < MBW; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int rb = m0 + (wm * MBW + i) * 32, cb = n0 + (wn * TN + j) * 32;
-        f32x4 sh1[4];
-        if constexpr (DN && !kShAll) load_shift(i, j, sh1);
+        const int q = i * TN + j;
+        if constexpr (DN) {
+          if (q + 1 < Q) load_shift(q + 1, sh[(q + 1) & 1]);
+        }
         // bf16 slot: 32 rows x 4 chunks of 16 B (8 bf16), chunk c of row r at
         // c ^ ((r / 4) % 4); this lane's 4 values are half `half` of chunk gq.
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
           float a0 = acc[i][j][4 * gq], a1 = acc[i][j][4 * gq + 1], a2 = acc[i][j][4 * gq + 2], a3 = acc[i][j][4 * gq + 3];
           if constexpr (DN) {
-            const f32x4 sh = kShAll ? shv[kShAll ? i : 0][kShAll ? j : 0][gq] : sh1[gq];
-            a0 = fmaf(a0, rinv[i], sh[0]);
-            a1 = fmaf(a1, rinv[i], sh[1]);
-            a2 = fmaf(a2, rinv[i], sh[2]);
-            a3 = fmaf(a3, rinv[i], sh[3]);
+            const f32x4 sv = sh[q & 1][gq];
+            a0 = fmaf(a0, nr.rinv[i], sv[0]);
+            a1 = fmaf(a1, nr.rinv[i], sv[1]);
+            a2 = fmaf(a2, nr.rinv[i], sv[2]);
+            a3 = fmaf(a3, nr.rinv[i], sv[3]);
           }
           if constexpr (EPI == kEpiGelu) {
             a0 = gelu_tanh_f(a0); a1 = gelu_tanh_f(a1); a2 = gelu_tanh_f(a2); a3 = gelu_tanh_f(a3);
@@ -476,14 +482,16 @@ __global__ void __launch_bounds__(T::NT) gemm_bf16_kernel(GemmArgs g, int nrt, i
   const int m0 = (in_strip / width) * T::BM, n0 = (sidx * strip + in_strip % width) * T::BN;
   const int nk = g.K / T::BK, kt0 = nk * slice / ksplit, kt1 = nk * (slice + 1) / ksplit;
   f32x16 acc[T::MBW][T::TN];
+  NormRows<T> nr;
+  if constexpr (DN && EPI != kEpiGatedResidual) gemm_norm_rows<T>(g, m0, nr);
   gemm_mainloop<T>(g, m0, n0, kt0, kt1 - kt0, L, acc);
   if constexpr (EPI == kEpiPartial) {
     GemmArgs gp = g;
     gp.out = g.part + (size_t)slice * g.M * g.N;
     gp.ldo = g.N;
-    gemm_epilogue<T, EPI>(gp, m0, n0, L, acc);
+    gemm_epilogue<T, EPI>(gp, m0, n0, L, acc, nr);
   } else {
-    gemm_epilogue<T, EPI, DN>(g, m0, n0, L, acc);
+    gemm_epilogue<T, EPI, DN>(g, m0, n0, L, acc, nr);
   }
 }
 
