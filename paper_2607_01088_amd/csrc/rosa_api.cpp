@@ -24,11 +24,14 @@ using namespace rosa;
 constexpr int kDeferMaxRows = 1024;
 
 // Most rows a lane-step may have for its attention launch to prefetch the
-// layer's weights into the caches (and the launch at most half the CUs' block
-// slots).  A step's weights (0.47 GB at the pi0 shape) do not stay in the
-// 256 MB memory-side cache, so each projection reads them from HBM; one robot's
-// call 8.50 -> 8.28 ms, 16 robots 12.30 -> 12.05 ms.
-constexpr int kPrefetchMaxRows = 1024;
+// layer's weights into the caches, and the fewest of the CUs' block slots the
+// launch must leave for that.  A step's weights (0.47 GB at the pi0 shape) do
+// not stay in the 256 MB memory-side cache, so each projection reads them from
+// HBM: one robot's call 8.50 -> 8.28 ms, 16 robots (264 - 528 rows) 12.30 -> 12.05,
+// a step of 33 (1,100 rows) 1,900 -> 1,880 us, alternating 64 robots (2,200 rows)
+// 18.67 -> 18.36 ms.  Larger launches fill the slots themselves.
+constexpr int kPrefetchMaxRows = 2560;
+constexpr int kMinPrefetchBlocks = 64;
 
 // Attention launch order.  The kernel's blocks are persistent: block b runs
 // the items of its own list one after another, and blocks reach the 8 XCDs
@@ -733,8 +736,8 @@ hipError_t run_attention(rosa_batch *b, const Plan &p, const Plan::Lane &ln, int
     a.items = items;
     a.ordered = lists + ln.list_at[v][k];
     a.n_blocks = ln.list_blocks[v][k];
-    if (prefetch && a.n_blocks > 0 && a.n_blocks <= kAttnBlocks / 2) {
-      a.n_prefetch = kAttnBlocks / 2;
+    if (prefetch && a.n_blocks > 0 && a.n_blocks <= kAttnBlocks - kMinPrefetchBlocks) {
+      a.n_prefetch = std::min(kAttnBlocks / 2, kAttnBlocks - a.n_blocks);
       std::copy(prefetch, prefetch + kPrefetchMats, a.prefetch);
     }
   }
