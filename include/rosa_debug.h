@@ -103,7 +103,8 @@ rosa_status rosa_debug_gemm_config(rosa_batch *b, int32_t cfg, int32_t *n_config
  * stream before the call returns.  Requests are independent, so results are
  * bitwise identical for any lane count; only the overlap of the sub-batches'
  * kernels changes.  n in [1, 4]; until this is called a bf16 handle takes one or
- * two lanes per call by the rows of its late steps, an fp32 one a single lane.  While per-kernel profiling is enabled every call runs one lane. */
+ * two lanes per call by the rows of its late steps, an fp32 one a single lane.
+ * While per-kernel profiling is enabled every call runs one lane. */
 rosa_status rosa_debug_set_lanes(rosa_batch *b, int32_t n);
 
 /* Per-kernel timing.  While enabled, every launch of the handle is bracketed

@@ -949,10 +949,10 @@ static float tile_cost(int c, int M, int N, float K, float b, int slices, int n_
 
 // Tile and K slices of a launch on the default path: the cheapest of the
 // direct tiles while they fill at most one round (with a workspace only: they
-// sum K in another order), of every LDS tile unsplit and, with a workspace, split over 2 .. kSplitMax slices of at
-// least 5 stages.  A slice's block costs its share of K plus 1.8 us; the launch
-// that sums the slices costs kReduceUs plus 1.5 us per million outputs and
-// slice (fit to 60 - 3000 rows, K = 2048 - 16384; the choice is 3% off the
+// sum K in another order), of every LDS tile unsplit and, with a workspace, split
+// over 2 .. kSplitMax slices of at least 5 stages.  A slice's block costs its
+// share of K plus 1.8 us; the launch that sums the slices costs 3.1 us (2.5 where
+// it takes the norm) plus 1.5 us per million outputs and slice (fit to 60 - 3000 rows, K = 2048 - 16384; the choice is 3% off the
 // best measured one on average).  An unsplit gated residual whose norm the
 // reduction would have taken pays for that norm: a launch of its own, or the
 // deferred norm's share of two epilogues.
