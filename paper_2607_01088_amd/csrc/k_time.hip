@@ -145,8 +145,8 @@ hipError_t launch_small_gemv(const float *X, int n, int K, const float *W, const
 // (up to 128 of K) in registers and streams weights: CT tiles of 16 columns per
 // step, every load of the next step in flight while the waves' partial sums meet in
 // LDS and are added in wave order.  Bound by streaming W once: the 0.23 GB
-// modulation weights take 50 us (a kernel on the vector units took 79 and a reduction
-// launch), a 2 MB time-MLP matrix 6 us (28).
+// modulation weights take 54 us (a kernel on the vector units took 79 and a reduction
+// launch 5), a 2 MB time-MLP matrix 9 us (28).
 constexpr int kTauRows = 16, kTauWaves = 8, kTauSteps = 4;
 template <int CT>
 __global__ void __launch_bounds__(64 * kTauWaves) tau_gemm_kernel(const float *__restrict__ X, int ldx, size_t x_stride,
