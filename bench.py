@@ -373,7 +373,7 @@ def _summarize_presets(out):
                         else "- |"))
     samples = [(w, j["cpu_baseline"]["sample"]) for w, j in rows if "cpu_baseline" in j]
     if samples:
-        lines += ["", "Oracle samples (float64 NumPy on the GPU box's host cores, scaled to the whole batch):"]
+        lines += ["", "Oracle samples (float64 NumPy on the GPU machine's host cores, scaled to the whole batch):"]
         lines += [f"- {w}: {smp}" for w, smp in samples]
     srcs = {f: hashlib.sha256(open(os.path.join(ROOT, "paper_2607_01088_amd", "csrc", f), "rb").read()).hexdigest()[:16]
             for f in ("k_attn.hip", "k_gemm.hip")}
