@@ -30,10 +30,10 @@ rosa_status rosa_debug_plan(const rosa_model_config *cfg, const rosa_capacity *c
 
 /* Host-only lane assignment of a request set (no GPU needed, nothing
  * enqueued): the lanes a bf16 call would split this set into when `lanes`
- * lanes are configured (rosa_debug_set_lanes), with the same rule as
- * rosa_generate_actions (at most n / 64 lanes).  lane_of[n] (by caller index)
- * receives each request's lane in [0, lanes).  Returns the status
- * rosa_generate_actions would return for this set. */
+ * lanes are forced (rosa_debug_set_lanes) or, with `lanes` 0, when none are,
+ * with the same rule as rosa_generate_actions.  lane_of[n] (by caller index)
+ * receives each request's lane.  Returns the status rosa_generate_actions
+ * would return for this set. */
 rosa_status rosa_debug_plan_lanes(const rosa_model_config *cfg, const rosa_capacity *cap,
                                   const rosa_request *reqs, int32_t n, int32_t lanes, int32_t *lane_of);
 

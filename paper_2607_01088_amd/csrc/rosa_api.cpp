@@ -644,10 +644,12 @@ hipError_t harvest_profile(rosa_batch *b) {
   return hipSuccess;
 }
 
-// Lanes of a call without a forced count (see kMinLateRows).  The requests are
-// not validated yet: an invalid set gets one lane and is refused by the plan.
-int auto_lanes(const rosa_request *reqs, int n, int max_steps) {
+// Lanes of a call: `forced` of them, or (0) one or two by its late rows (see
+// kMinLateRows), and at most one per kMinLaneRequests requests.  The requests are
+// not validated yet: an invalid set gets some count and is refused by the plan.
+int call_lanes(const rosa_request *reqs, int n, int max_steps, int forced) {
   if (!reqs || n < 2 * kMinLaneRequests) return 1;
+  if (forced > 0) return std::min(forced, n / kMinLaneRequests);
   auto steps = [&](int i) { return std::min((int64_t)reqs[i].num_steps - reqs[i].start_step, (int64_t)max_steps); };
   int64_t k_max = 0, late = 0;
   for (int i = 0; i < n; ++i) k_max = std::max(k_max, steps(i));
@@ -1010,10 +1012,8 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
     if (b->poisoned) return fail(b, ROSA_E_DEVICE, "handle is poisoned by an earlier device error");
     Plan p;
     std::string err;
-    // Lanes only without per-kernel profiling (its events live on one stream)
-    // and with enough requests for each lane.
-    const int lanes = b->prof ? 1 : std::max(1, std::min(b->lanes > 0 ? b->lanes : auto_lanes(reqs, n, max_steps),
-                                                         n / kMinLaneRequests));
+    // Lanes only without per-kernel profiling (its events live on one stream).
+    const int lanes = b->prof ? 1 : call_lanes(reqs, n, max_steps, b->lanes);
     rosa_status st = build_plan(&b->cfg, &b->cap, reqs, n, true, b->bf16, lanes, p, err, max_steps);
     if (st != ROSA_OK) return fail(b, st, err);
     if (n == 0) return ROSA_OK;
@@ -1307,12 +1307,12 @@ rosa_status rosa_debug_attn_lists(const rosa_model_config *cfg, const rosa_capac
 rosa_status rosa_debug_plan_lanes(const rosa_model_config *cfg, const rosa_capacity *cap, const rosa_request *reqs,
                                   int32_t n, int32_t lanes, int32_t *lane_of) {
   try {
-    if (!cfg || !cap || !lane_of || lanes < 1 || lanes > kMaxLanes) return ROSA_E_INVALID;
+    if (!cfg || !cap || !lane_of || lanes < 0 || lanes > kMaxLanes) return ROSA_E_INVALID;
     rosa_status st = check_config(cfg);
     if (st != ROSA_OK) return st;
     st = check_capacity(cap);
     if (st != ROSA_OK) return st;
-    const int nl = cfg->dtype == ROSA_BF16 ? std::max(1, std::min<int>(lanes, n / kMinLaneRequests)) : 1;
+    const int nl = cfg->dtype == ROSA_BF16 ? call_lanes(reqs, n, INT32_MAX, lanes) : 1;
     Plan p;
     std::string err;
     st = build_plan(cfg, cap, reqs, n, true, cfg->dtype == ROSA_BF16, nl, p, err);

@@ -266,7 +266,8 @@ def last_error_global() -> str:
 
 
 def plan_lanes(shape, dtype: str, cap: Capacity, reqs: Sequence[Request], lanes: int):
-    """Host-only lane assignment (rosa_debug_plan_lanes): (status, lane of each request)."""
+    """Host-only lane assignment (rosa_debug_plan_lanes) with `lanes` lanes forced, or
+    (0) as an unforced call chooses: (status, lane of each request)."""
     lib = load()
     cfg = model_config(shape, dtype)
     n = len(reqs)

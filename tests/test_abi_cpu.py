@@ -106,6 +106,26 @@ def test_plan_lanes_balance_and_cover_every_request():
     assert st == rosa.ROSA_OK and set(lanes) == {0}
 
 
+@pytest.mark.parametrize("specs,want", [
+    ([(50, 10)] * 127, 1),                               # fewer than 64 requests per lane
+    ([(49, 10)] * 126 + [(13, 10)] * 2, 2),              # 6,200 rows all along
+    ([(49, 10)] * 126 + [(13, 10), (12, 10)], 1),        # 6,199
+    ([(50, 10)] * 124 + [(50, 5)] * 132, 2),             # 6,200 of 12,800 rows late
+    ([(50, 10)] * 123 + [(50, 5)] * 132, 1),             # 6,150
+    ([(50, 10)] * 100 + [(50, 8)] * 156, 2),             # eight of ten steps are late too
+    ([(50, 10)] * 100 + [(50, 7)] * 156, 1),             # seven are not
+    ([(50, 1)] * 124, 1),                                # 6,200 rows of 124 requests
+    ([(50, 10, 9)] * 124 + [(50, 5, 4)] * 132, 2),       # one step each: every row is late
+])
+def test_plan_lanes_automatic_choice(specs, want):
+    """Without a forced count (lanes 0) a call of at least 128 requests takes two
+    lanes where at least 6,200 rows are active three quarters through its steps."""
+    reqs = [req(600, s[0], s[1], start_step=s[2] if len(s) > 2 else 0) for s in specs]
+    cap = rosa.capacity(256, 50, 256 * 50, 10, 256 * 600)
+    st, lanes = rosa.plan_lanes(PI0_SHAPE, "bf16", cap, reqs, 0)
+    assert st == rosa.ROSA_OK and sorted(set(lanes)) == list(range(want))
+
+
 def _walk_lists(nb, item_of, nxt):
     """Follow each block's chain; returns the item lists per block."""
     seen = [False] * len(item_of)
