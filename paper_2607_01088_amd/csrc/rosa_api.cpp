@@ -646,9 +646,10 @@ hipError_t harvest_profile(rosa_batch *b) {
 
 // Lanes of a call: `forced` of them, or (0) one or two by its late rows (see
 // kMinLateRows), and at most one per kMinLaneRequests requests.  The requests are
-// not validated yet: an invalid set gets some count and is refused by the plan.
-int call_lanes(const rosa_request *reqs, int n, int max_steps, int forced) {
-  if (!reqs || n < 2 * kMinLaneRequests) return 1;
+// not validated yet: an invalid set gets some count and is refused by the plan,
+// one above the capacity without a look at its requests.
+int call_lanes(const rosa_capacity &cap, const rosa_request *reqs, int n, int max_steps, int forced) {
+  if (!reqs || n < 2 * kMinLaneRequests || n > cap.max_requests) return 1;
   if (forced > 0) return std::min(forced, n / kMinLaneRequests);
   auto steps = [&](int i) { return std::min((int64_t)reqs[i].num_steps - reqs[i].start_step, (int64_t)max_steps); };
   int64_t k_max = 0, late = 0;
@@ -1013,7 +1014,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
     Plan p;
     std::string err;
     // Lanes only without per-kernel profiling (its events live on one stream).
-    const int lanes = b->prof ? 1 : call_lanes(reqs, n, max_steps, b->lanes);
+    const int lanes = b->prof ? 1 : call_lanes(b->cap, reqs, n, max_steps, b->lanes);
     rosa_status st = build_plan(&b->cfg, &b->cap, reqs, n, true, b->bf16, lanes, p, err, max_steps);
     if (st != ROSA_OK) return fail(b, st, err);
     if (n == 0) return ROSA_OK;
@@ -1312,7 +1313,7 @@ rosa_status rosa_debug_plan_lanes(const rosa_model_config *cfg, const rosa_capac
     if (st != ROSA_OK) return st;
     st = check_capacity(cap);
     if (st != ROSA_OK) return st;
-    const int nl = cfg->dtype == ROSA_BF16 ? call_lanes(reqs, n, INT32_MAX, lanes) : 1;
+    const int nl = cfg->dtype == ROSA_BF16 ? call_lanes(*cap, reqs, n, INT32_MAX, lanes) : 1;
     Plan p;
     std::string err;
     st = build_plan(cfg, cap, reqs, n, true, cfg->dtype == ROSA_BF16, nl, p, err);

@@ -3,12 +3,14 @@ function, validation is all-or-nothing with the documented status codes, and
 the batch plan (K-descending order, token offsets, active tokens per step,
 distinct flow times) is right.  No GPU needed."""
 import ctypes as C
+import subprocess
+import sys
 
 import pytest
 
 from paper_2607_01088_amd import rosa
 from synthetic import PI0_SHAPE, TINY_SHAPE
-from tests.helpers import declared_functions
+from tests.helpers import ROOT, declared_functions
 
 FAKE = 0x1000   # non-NULL device address; host planning never dereferences it
 
@@ -124,6 +126,23 @@ def test_plan_lanes_automatic_choice(specs, want):
     cap = rosa.capacity(256, 50, 256 * 50, 10, 256 * 600)
     st, lanes = rosa.plan_lanes(PI0_SHAPE, "bf16", cap, reqs, 0)
     assert st == rosa.ROSA_OK and sorted(set(lanes)) == list(range(want))
+
+
+def test_lane_choice_reads_no_request_of_a_refused_set():
+    """More requests than the capacity holds are refused before any of them is
+    read: the array here holds four (in a child process, since reading on past
+    it ends the process)."""
+    code = """if 1:
+        import ctypes as C
+        from paper_2607_01088_amd import rosa
+        from synthetic import PI0_SHAPE
+        cfg, cap = rosa.model_config(PI0_SHAPE, "bf16"), rosa.capacity(4, 50, 200, 10, 4000)
+        arr, out = (rosa.Request * 4)(), (C.c_int32 * 4)()
+        st = rosa.load().rosa_debug_plan_lanes(C.byref(cfg), C.byref(cap), arr, 1 << 27, 0, out)
+        raise SystemExit(st)
+    """
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, timeout=120)
+    assert res.returncode == rosa.ROSA_E_CAPACITY
 
 
 def _walk_lists(nb, item_of, nxt):
