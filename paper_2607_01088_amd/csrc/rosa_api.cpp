@@ -18,9 +18,11 @@
 
 using namespace rosa;
 
-// Most rows a lane-step may have for its unsplit output projection and
-// MLP-down to defer their norms to the next product.  Above it a separate
-// norm launch costs less than the completing products' longer epilogues.
+// Most rows a call may have active at a step for that step's unsplit output
+// projections and MLP-downs to defer their norms to the next product.  Above it
+// a separate norm launch costs less than the completing products' longer
+// epilogues.  The call's rows, not a lane's: a deferred norm rounds another
+// operand, so the lane count must not decide it.
 constexpr int kDeferMaxRows = 1024;
 
 // Most rows a lane-step may have for its attention launch to prefetch the
@@ -1046,7 +1048,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
     if (b->bf16 && b->dn_ss && b->kb_rows > 0 && D.d % 256 == 0 && D.d <= 1024) {
       for (const Plan::Lane &ln : p.lanes)
         for (int k = 0; k < p.Kmax && !defer_on; ++k) {
-          if (ln.m[k] == 0 || ln.m[k] > kDeferMaxRows) continue;
+          if (ln.m[k] == 0 || p.m_k[k] > kDeferMaxRows) continue;
           GemmArgs t{};
           if (split_ok) { t.part = b->gemm_part; t.part_floats = b->gemm_part_floats; }
           t.M = ln.m[k]; t.N = D.d; t.ldo = D.d; t.epi = kEpiGatedResidual;
@@ -1095,7 +1097,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
         const int32_t *row_req = b->row_req + r0;
         e = timed(b, kcInProj, [&] { return launch_in_proj(x, M, D.A, b->w_in, b->b_in, D.d, h, st); });
         const int fshift = D.L * (int)d6, fscale = D.L * (int)d6 + D.d;
-        float *dss = defer_on && M <= kDeferMaxRows ? b->dn_ss + r0 * (D.d / 32) : nullptr;
+        float *dss = defer_on && p.m_k[k] <= kDeferMaxRows ? b->dn_ss + r0 * (D.d / 32) : nullptr;
         // The deferred norm's producer outputs (t into u) and its completion
         // in the product that reads u, from this layer's shift table.
         auto defer_out = [&](GemmArgs &gx, int scale_off) {

@@ -377,6 +377,27 @@ def test_lane_counts_bitwise_identical(pi0_expert):
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("few", [16, 24, 44])
+def test_lane_counts_bitwise_identical_where_norms_defer(pi0_expert, few):
+    """The same with late steps of `few` requests of horizon 50 (800, 1,200 and
+    2,200 rows): a lane's rows lie below the row limit of the deferred norms
+    where the whole call's lie below, above, and above even in two lanes."""
+    e, _ = pi0_expert
+    reqs = [custom_request(PI0_SHAPE, "bf16", 65 + 3 * i, 50, 4 if i < few else 2, seed=900 + i) for i in range(128)]
+    db = _rosa().DeviceBatch(reqs, "bf16")
+    outs = []
+    try:
+        for lanes in (1, 2):
+            e.set_lanes(lanes)
+            e.generate(db.structs)
+            torch.cuda.synchronize()
+            outs.append(db.results())
+    finally:
+        e.set_lanes(2)
+    for i, (a, b) in enumerate(zip(*outs)):
+        assert np.isfinite(a).all() and np.array_equal(a, b), i
+
+
 # ------------------------------------------------------------------ ABI errors on a live handle
 
 def test_invalid_request_enqueues_nothing(pi0_expert):
