@@ -26,13 +26,18 @@ using namespace rosa;
 constexpr int kDeferMaxRows = 1024;
 
 // Most rows a lane-step may have for its attention launch to prefetch the
-// layer's weights into the caches, and the fewest of the CUs' block slots the
-// launch must leave for that.  A step's weights (0.47 GB at the pi0 shape) do
-// not stay in the 256 MB memory-side cache, so each projection reads them from
-// HBM: one robot's call 8.50 -> 8.28 ms, 16 robots (264 - 528 rows) 12.30 -> 12.05,
-// a step of 33 (1,100 rows) 1,900 -> 1,880 us, alternating 64 robots (2,200 rows)
-// 18.67 -> 18.36 ms.  Larger launches fill the slots themselves.
+// layer's weights into the caches, the most bytes of those weights, and the
+// fewest of the CUs' block slots the launch must leave for it.  A step's weights
+// (0.47 GB at the pi0 shape) do not stay in the 256 MB memory-side cache, so each
+// projection reads them from HBM: at the pi0 shape (26 MB a layer) one robot's
+// call 8.13 -> 7.89 ms, 4 robots 10.37 -> 10.18, 16 15.36 -> 14.53, 40 23.25 -> 22.9.
+// Launches of more rows fill the slots themselves.  A layer that the XCDs' L2s
+// (4 MB each, 32 MB together) cannot hold evicts its own first lines and keeps
+// the launch waiting for what it reads: 50 MB (width 1536) 4.49 -> 4.66 ms for one
+// robot and 14.6 -> 14.0 for 40, 86 MB (2048) 3.80 -> 4.23 and 14.3 -> 14.3, 210 MB
+// (4096) 3.57 -> 4.30 and 14.65 -> 14.65.
 constexpr int kPrefetchMaxRows = 2560;
+constexpr size_t kPrefetchMaxBytes = (size_t)32 << 20;
 constexpr int kMinPrefetchBlocks = 64;
 
 // Attention launch order.  The kernel's blocks are persistent: block b runs
@@ -1079,6 +1084,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
     }
     const size_t d6 = (size_t)6 * D.d;
     const size_t es = b->esz;
+    const bool prefetch_ok = b->bf16 && ((size_t)D.qkv_dim + D.o_dim + 2 * (size_t)D.dff) * D.d * es <= kPrefetchMaxBytes;
     for (int k = 0; k < p.Kmax && e == hipSuccess; ++k) {
       for (int li = 0; li < nl && e == hipSuccess; ++li) {
         const Plan::Lane &ln = p.lanes[li];
@@ -1136,7 +1142,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
               {(uint8_t *)b->wt_up + (size_t)l * D.dff * D.d * es, D.d / 32, (uint32_t)D.dff * 64},
               {(uint8_t *)b->wt_down + (size_t)l * D.d * D.dff * es, D.dff / 32, (uint32_t)D.d * 64},
               {(uint8_t *)b->wt_qkv + (size_t)lq * D.qkv_dim * D.d * es, D.d / 32, (uint32_t)D.qkv_dim * 64}};
-          e = run_attention(b, p, ln, k, l, b->qkv, b->o, st, b->kb_rows, b->bf16 && M <= kPrefetchMaxRows ? pf : nullptr);
+          e = run_attention(b, p, ln, k, l, b->qkv, b->o, st, b->kb_rows, prefetch_ok && M <= kPrefetchMaxRows ? pf : nullptr);
           if (e != hipSuccess) break;
           GemmArgs go{};
           if (split_ok) { go.part = b->gemm_part; go.part_floats = b->gemm_part_floats; }
