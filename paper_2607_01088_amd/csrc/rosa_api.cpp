@@ -195,11 +195,18 @@ constexpr int kMaxLanes = 4;
 constexpr int kMinLaneRequests = 64;  // a batch splits into lanes only with at least this many requests per lane
 // Without a forced lane count a call of 2 kMinLaneRequests requests or more runs
 // two lanes if at least this many rows are still active three quarters through
-// its steps.  Two lanes fill each other's gaps but halve every launch: 128
-// requests of horizon 50 (6,400 rows all along) 53.6 ms in one lane, 52.3 in
-// two; 384 mixed ones (12,100 rows, half of them for half the steps) 69.1 and
-// 71.1; 256 mixed ones 48.7 and 50.9; 512 mixed ones (8,400 late rows) 100.4 and 97.6.
+// its steps.  Two lanes fill each other's gaps but halve every launch (one lane and
+// two, ms): 130 requests of horizon 43 (5,590 rows all along) 45.5 and 49.4, 384
+// mixed ones (12,060 rows, 6,100 late) 68.7 and 73.7, 128 of 50 (6,400) 51.2 and 52.7
+// on one card, 52.7 and 52.0 on another, 200 of 33 (6,600) 51.0 and 50.6, 448 mixed
+// (14,036, 7,250 late) 82.6 and 81.2, 512 of 50 (25,600) 191.7 and 178.9.
 constexpr int kMinLateRows = 6200;
+// A call of at most this many rows runs one lane whatever its request count, so
+// that its products may sum K in slices: 128 requests of 1 row 13.6 ms in two lanes
+// of unsliced products, 13.8 in one, 11.8 in one with slices; of 4 rows 15.4,
+// 15.7 and 15.5; of 8 rows 23.5, 18.8 and 18.7; at 2,560 rows (160 of 16) slices
+// lose (30.0 and 30.4 in one lane).
+constexpr int kSmallCallRows = 1024;
 
 enum KernelClass {
   kcTime = 0, kcSetup, kcInProj, kcModNorm, kcGemmQKV, kcAttention, kcMerge, kcGemmO, kcGemmUp,
@@ -651,12 +658,18 @@ hipError_t harvest_profile(rosa_batch *b) {
   return hipSuccess;
 }
 
-// Lanes of a call: `forced` of them, or (0) one or two by its late rows (see
-// kMinLateRows), and at most one per kMinLaneRequests requests.  The requests are
-// not validated yet: an invalid set gets some count and is refused by the plan,
-// one above the capacity without a look at its requests.
+// A call of few requests or few rows: always one lane.
+bool small_call(int n, int64_t rows) { return n < 2 * kMinLaneRequests || rows <= kSmallCallRows; }
+
+// Lanes of a call: one if it is small; else `forced` of them, or (0) one or two
+// by its late rows (see kMinLateRows), and at most one per kMinLaneRequests
+// requests.  The requests are not validated yet: an invalid set gets some count
+// and is refused by the plan, one above the capacity without a look at its requests.
 int call_lanes(const rosa_capacity &cap, const rosa_request *reqs, int n, int max_steps, int forced) {
-  if (!reqs || n < 2 * kMinLaneRequests || n > cap.max_requests) return 1;
+  if (!reqs || n < 1 || n > cap.max_requests) return 1;
+  int64_t rows = 0;
+  for (int i = 0; i < n; ++i) rows += std::max(reqs[i].horizon, 0);
+  if (small_call(n, rows)) return 1;
   if (forced > 0) return std::min(forced, n / kMinLaneRequests);
   auto steps = [&](int i) { return std::min((int64_t)reqs[i].num_steps - reqs[i].start_step, (int64_t)max_steps); };
   int64_t k_max = 0, late = 0;
@@ -1041,9 +1054,9 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
       });
     const int nl = (int)p.lanes.size();
     // The products may sum K in other orders (slices over blocks) only in
-    // calls too small for two lanes: a request's actions are then the same
+    // calls that always run one lane: a request's actions are then the same
     // whatever number of lanes a larger call runs.
-    const bool split_ok = n < 2 * kMinLaneRequests;
+    const bool split_ok = small_call(n, p.M0);
     // Deferred norms: every unsplit output projection and MLP-down leaves t
     // and the row sums of squares for the next product, which completes the
     // norm; the shift halves are computed once per call, when some launch of

@@ -128,6 +128,21 @@ def test_plan_lanes_automatic_choice(specs, want):
     assert st == rosa.ROSA_OK and sorted(set(lanes)) == list(range(want))
 
 
+@pytest.mark.parametrize("specs,want", [
+    ([(8, 10)] * 128, 1),                    # 1,024 rows
+    ([(8, 10)] * 127 + [(9, 10)], 2),        # 1,025
+    ([(50, 10)] * 127, 1),                   # fewer than 64 requests per lane
+    ([(1, 10)] * 256, 1),
+])
+def test_calls_of_few_rows_keep_one_lane(specs, want):
+    """A call of at most 1,024 rows runs one lane whatever is forced, so that its
+    products may be sliced."""
+    reqs = [req(600, H, K) for H, K in specs]
+    cap = rosa.capacity(256, 50, 256 * 50, 10, 256 * 600)
+    st, lanes = rosa.plan_lanes(PI0_SHAPE, "bf16", cap, reqs, 2)
+    assert st == rosa.ROSA_OK and sorted(set(lanes)) == list(range(want))
+
+
 def test_lane_choice_reads_no_request_of_a_refused_set():
     """More requests than the capacity holds are refused before any of them is
     read: the array here holds four (in a child process, since reading on past

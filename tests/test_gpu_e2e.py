@@ -398,6 +398,29 @@ def test_lane_counts_bitwise_identical_where_norms_defer(pi0_expert, few):
         assert np.isfinite(a).all() and np.array_equal(a, b), i
 
 
+@pytest.mark.parametrize("H", [1, 8])
+def test_many_requests_of_few_rows(pi0_expert, H):
+    """128 requests of one and of eight rows (up to 1,024 rows): one lane with
+    sliced products, the same actions when two lanes are forced, four sampled
+    requests against the oracle."""
+    e, w = pi0_expert
+    reqs = [custom_request(PI0_SHAPE, "bf16", 40 + 5 * i, H, 3, seed=1200 + i) for i in range(128)]
+    db = _rosa().DeviceBatch(reqs, "bf16")
+    outs = []
+    try:
+        for lanes in (1, 2):
+            e.set_lanes(lanes)
+            e.generate(db.structs)
+            torch.cuda.synchronize()
+            outs.append(db.results())
+    finally:
+        e.set_lanes(2)
+    for i, (a, b) in enumerate(zip(*outs)):
+        assert np.isfinite(a).all() and np.array_equal(a, b), i
+    pick = [0, 41, 90, 127]
+    _check([outs[0][i] for i in pick], [reqs[i] for i in pick], w, PI0_SHAPE, 1e-2, f"128 requests of {H} rows")
+
+
 # ------------------------------------------------------------------ ABI errors on a live handle
 
 def test_invalid_request_enqueues_nothing(pi0_expert):
