@@ -96,13 +96,14 @@ rosa_status rosa_debug_gemm(rosa_batch *b, int32_t which, int32_t layer, const v
  * n_configs may be NULL. */
 rosa_status rosa_debug_gemm_config(rosa_batch *b, int32_t cfg, int32_t *n_configs);
 
-/* Number of lanes: a call with at least 64 requests per lane splits its
- * requests into that many sub-batches of similar work, each on its own stream
- * (the handle's stream for lane 0, internal default-priority streams for the
- * others), forked after the time conditioning and joined back on the handle's
- * stream before the call returns.  Requests are independent, so results are
- * bitwise identical for any lane count; only the overlap of the sub-batches'
- * kernels changes.  n in [1, 4]; until this is called a bf16 handle takes one or
+/* Number of lanes: a call with at least 64 requests per lane and more than 1024
+ * rows splits its requests into that many sub-batches of similar work, each on
+ * its own stream (the handle's stream for lane 0, internal default-priority
+ * streams for the others), forked after the time conditioning and joined back on
+ * the handle's stream before the call returns.  Requests are independent and
+ * no rounding depends on the lanes, so results are bitwise identical for any
+ * lane count; only the overlap of the sub-batches' kernels changes.  n in [1, 4]
+ * forces a count; 0, the state of a new handle, lets a bf16 handle take one or
  * two lanes per call by the rows of its late steps, an fp32 one a single lane.
  * While per-kernel profiling is enabled every call runs one lane. */
 rosa_status rosa_debug_set_lanes(rosa_batch *b, int32_t n);

@@ -1547,8 +1547,8 @@ rosa_status rosa_debug_gemm(rosa_batch *b, int32_t which, int32_t layer, const v
 
 rosa_status rosa_debug_set_lanes(rosa_batch *b, int32_t n) {
   if (!b) return ROSA_E_INVALID;
-  if (n < 1 || n > kMaxLanes) return fail(b, ROSA_E_INVALID, "lane count out of range");
-  b->lanes = n;
+  if (n < 0 || n > kMaxLanes) return fail(b, ROSA_E_INVALID, "lane count out of range");
+  b->lanes = n > 0 || b->bf16 ? n : 1;   // without a forced count fp32 calls run one lane
   return ROSA_OK;
 }
 

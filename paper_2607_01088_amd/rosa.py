@@ -433,7 +433,8 @@ class ActionExpert:
                                              None if gate is None else gate.data_ptr()))
 
     def set_lanes(self, n: int) -> None:
-        """Number of concurrent sub-batches (streams) per call."""
+        """Number of concurrent sub-batches (streams) per call; 0: chosen per call,
+        as on a new handle."""
         self._check(self.lib.rosa_debug_set_lanes(self.handle, n))
 
     def gemm_config(self, cfg: int) -> int:

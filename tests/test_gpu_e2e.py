@@ -371,7 +371,7 @@ def test_lane_counts_bitwise_identical(pi0_expert):
             torch.cuda.synchronize()
             outs.append(db.results())
     finally:
-        e.set_lanes(2)
+        e.set_lanes(0)
     for o in outs[1:]:
         for a, b in zip(o, outs[0]):
             assert np.array_equal(a, b)
@@ -393,9 +393,33 @@ def test_lane_counts_bitwise_identical_where_norms_defer(pi0_expert, few):
             torch.cuda.synchronize()
             outs.append(db.results())
     finally:
-        e.set_lanes(2)
+        e.set_lanes(0)
     for i, (a, b) in enumerate(zip(*outs)):
         assert np.isfinite(a).all() and np.array_equal(a, b), i
+
+
+def test_lane_count_can_be_given_back(pi0_expert):
+    """A forced lane count can be undone (0); counts outside [0, 4] are refused
+    and leave the handle usable."""
+    rosa = _rosa()
+    e, _ = pi0_expert
+    reqs = make_requests(PRESETS["factory_b256"], indices=list(range(130)))
+    db = rosa.DeviceBatch(reqs, "bf16")
+    try:
+        e.set_lanes(4)
+        for bad in (-1, 5):
+            with pytest.raises(rosa.RosaError) as err:
+                e.set_lanes(bad)
+            assert err.value.status == rosa.ROSA_E_INVALID
+        e.generate(db.structs)
+        torch.cuda.synchronize()
+        forced = db.results()
+    finally:
+        e.set_lanes(0)
+    e.generate(db.structs)
+    torch.cuda.synchronize()
+    for a, b in zip(forced, db.results()):
+        assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("H", [1, 8])
@@ -414,7 +438,7 @@ def test_many_requests_of_few_rows(pi0_expert, H):
             torch.cuda.synchronize()
             outs.append(db.results())
     finally:
-        e.set_lanes(2)
+        e.set_lanes(0)
     for i, (a, b) in enumerate(zip(*outs)):
         assert np.isfinite(a).all() and np.array_equal(a, b), i
     pick = [0, 41, 90, 127]
