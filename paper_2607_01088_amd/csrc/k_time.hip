@@ -7,6 +7,7 @@
 // bf16 for the pi0 shape) are streamed once per call for all distinct taus
 // together: the kernels are HBM-bound on weight bytes.
 #include <algorithm>
+#include <cfloat>
 
 #include "rosa_device.h"
 #include "rosa_internal.h"
@@ -141,7 +142,9 @@ hipError_t launch_small_gemv(const float *X, int n, int K, const float *W, const
 // fp32 inputs: X = hi + mid + lo in bf16, each the rounded remainder of
 // the ones before (24 bits and more together), so three
 // v_mfma_f32_16x16x32_bf16 per weight fragment form the exact products and
-// accumulate them in fp32.  The eight waves split K; a wave keeps its share of X
+// accumulate them in fp32.  Values beyond bf16's range have no such split (inf - inf,
+// or 0 times an infinite weight): four outputs among which one comes out infinite or NaN
+// are summed again from X itself.  The eight waves split K; a wave keeps its share of X
 // (up to 128 of K) in registers and streams weights: CT tiles of 16 columns per
 // step, every load of the next step in flight while the waves' partial sums meet in
 // LDS and are added in wave order.  Bound by streaming W once: the 0.23 GB
@@ -244,6 +247,17 @@ __global__ void __launch_bounds__(64 * kTauWaves) tau_gemm_kernel(const float *_
         for (int k = 0; k < 4; ++k) v[k] += p[k];
       }
       if (t < n && col < N) {
+        const bool finite = fabsf(v[0]) <= FLT_MAX && fabsf(v[1]) <= FLT_MAX && fabsf(v[2]) <= FLT_MAX && fabsf(v[3]) <= FLT_MAX;
+        if (__builtin_expect(!finite, 0)) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[k] = 0.f;
+          for (int i = 0; i < K; ++i) {
+            const float x = X[(size_t)t * ldx + i];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              v[k] = fmaf(x, (float)W[((size_t)(i >> 5) * N + col + k) * 32 + (i & 31)], v[k]);
+          }
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           if (b) v[k] += b[col + k];

@@ -122,6 +122,41 @@ def test_time_conditioning_bf16_shapes(d, dt, n):
         e.close()
 
 
+@pytest.mark.parametrize("d", [128, 1152])
+@pytest.mark.parametrize("what", ["inf", "above_bf16", "inf_weight"])
+def test_time_conditioning_bf16_beyond_finite(d, what):
+    """An infinite input of the last product, one that only bf16 takes for infinite,
+    and an infinite weight: infinities keep their sign, and nothing becomes NaN
+    that fp32 products would not make so."""
+    from synthetic import ModelShape, make_weights
+    from paper_2607_01088_amd import rosa
+    sh = ModelShape(n_layers=1, d_model=d, n_q_heads=4, n_kv_heads=1, head_dim=32, d_mlp=128, action_dim=7, time_emb_dim=64)
+    w = make_weights(sh, "bf16", seed=8)
+    if what == "inf":
+        w["b_t2"][3] = np.inf
+    elif what == "above_bf16":
+        w["b_t2"][3] = 3.4e38
+    else:
+        w["w_mod"][0, 3, ::5] = np.inf
+    e = rosa.ActionExpert(sh, "bf16", w, rosa.capacity(1, 4, 4, 4, 4))
+    try:
+        taus = [0.0, 0.25, 0.625]
+        out = torch.empty((len(taus), 8 * d), dtype=torch.float32, device="cuda")
+        e.time_conditioning(taus, out)
+        got = out.cpu().numpy()
+        om = OracleModel(w, sh)
+        for i, tau in enumerate(taus):
+            with np.errstate(all="ignore"):
+                s = om.time_condition(tau)
+                ref = np.concatenate([np.concatenate(om.block_modulation(s, 0)), np.concatenate(om.final_modulation(s))])
+            fin = np.isfinite(ref)
+            assert fin.any() == (what != "inf") and fin.all() == (what == "above_bf16")
+            assert np.array_equal(got[i][~fin], ref[~fin].astype(np.float32), equal_nan=True)
+            assert not fin.any() or rel_l2(got[i][fin] * 2.0**-64, ref[fin] * 2.0**-64) < 1e-5
+    finally:
+        e.close()
+
+
 # ------------------------------------------------------------------ projections
 
 @pytest.mark.parametrize("which", ["tiny_fp32", "tiny_bf16", "pi0_bf16"])
