@@ -236,10 +236,6 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs &g, int m0, int n0,
   __syncthreads();                          // every wave is past its last stage read: LDS is free
 }
 
-// Epilogue of the tile at (m0, n0) from acc; stages through the ring's LDS,
-// which must be free (gemm_mainloop ends that way).  DN: the deferred norm's
-// part of the epilogue (outputs t and the row sums of squares after a gated
-// residual; the norm's completion before a bf16 store).
 // 1 / rms and modulation row of this lane's row in each of its 32-row blocks,
 // for the completion of a deferred norm.
 template <typename T>
@@ -276,6 +272,10 @@ __device__ __forceinline__ void gemm_norm_rows(const GemmArgs &g, int m0, NormRo
   }
 }
 
+// Epilogue of the tile at (m0, n0) from acc; stages through the ring's LDS,
+// which must be free (gemm_mainloop ends that way).  DN: the deferred norm's
+// part of the epilogue (outputs t and the row sums of squares after a gated
+// residual; the norm's completion before a bf16 store).
 template <typename T, int EPI, bool DN = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int m0, int n0, uint8_t *L,
                                               f32x16 (&acc)[T::MBW][T::TN], const NormRows<T> &nr) {
@@ -296,11 +296,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int m0, int n0,
     float *H = reinterpret_cast<float *>(g.out);
     // Gate rows of every row this lane touches, loaded once up front so that
     // no gate load waits for its row's modulation index (32-bit offsets: the
-    // gate table has far fewer than 2^31 elements).  Tiles of 16 waves have no
-    // registers to spare (128 per lane) and look the index up per use.
-    constexpr bool kHoist = T::NW < 16 && EPI == kEpiGatedResidual;
-    int goff[kHoist ? MBW : 1][4];
-    if constexpr (kHoist) {
+    // gate table has far fewer than 2^31 elements).
+    int goff[EPI == kEpiGatedResidual ? MBW : 1][4];
+    if constexpr (EPI == kEpiGatedResidual) {
 #pragma unroll
       for (int i = 0; i < MBW; ++i)
 #pragma unroll
@@ -313,17 +311,15 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int m0, int n0,
     // 4 (lane % 8) .. + 3.  The residual and gate rows of tile q + 1 are
     // requested before tile q is combined, so each tile's global loads wait
     // behind the previous tile's work instead of stalling on their own
-    // (two register sets; 16-wave tiles, and tiles small enough to run two
-    // blocks per CU, have no registers to spare and load each tile's rows
-    // just before use).
+    // (two register sets; tiles small enough to run two blocks per CU, and the
+    // deferred norm's, which load scale rows too, have no registers to spare and
+    // load each tile's rows just before use).
     constexpr int Q = MBW * TN;
     constexpr bool kTwoBlocks = T::NST * T::SBYTES <= 80 * 1024;
-    constexpr int NB = (EPI == kEpiGatedResidual && T::NW < 16 && !kTwoBlocks && !DN) ? 2 : 1;
+    constexpr int NB = (EPI == kEpiGatedResidual && !kTwoBlocks && !DN) ? 2 : 1;
     float4 hv[NB][4], gt[NB][4];
-    // The deferred norm's scale rows load with the tile's other rows, except in
-    // 16-wave tiles (no registers to spare), which load them at use.
-    constexpr bool kScvAhead = DN && T::NW < 16;
-    float4 scv[kScvAhead ? NB : 1][4];
+    // The deferred norm's scale rows load with the tile's other rows.
+    float4 scv[DN ? NB : 1][4];
     const int col0 = (lane & 7) * 4;
     auto load_rows = [&](int q, int buf) __attribute__((always_inline)) {
       const int i = q / TN, j = q % TN;
@@ -333,12 +329,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int m0, int n0,
         const int row = rb + 8 * p + (lane >> 3);
         if (row < g.M && col < g.N) {
           hv[buf][p] = *reinterpret_cast<const float4 *>(H + (size_t)row * g.ldo + col);
-          if constexpr (kHoist) gt[buf][p] = *reinterpret_cast<const float4 *>(g.gate + goff[i][p] + col);
-          else gt[buf][p] = *reinterpret_cast<const float4 *>(g.gate + (size_t)g.rowmod[row] * g.gate_stride + col);
-          if constexpr (kScvAhead) {
-            if constexpr (kHoist) scv[buf][p] = *reinterpret_cast<const float4 *>(g.dscale + goff[i][p] + col);
-            else scv[buf][p] = *reinterpret_cast<const float4 *>(g.dscale + (size_t)g.rowmod[row] * g.gate_stride + col);
-          }
+          gt[buf][p] = *reinterpret_cast<const float4 *>(g.gate + goff[i][p] + col);
+          if constexpr (DN) scv[buf][p] = *reinterpret_cast<const float4 *>(g.dscale + goff[i][p] + col);
         }
       }
     };
@@ -378,9 +370,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int m0, int n0,
             h.w = h.w + gt[buf][p].w * v[p].w;
             *reinterpret_cast<float4 *>(H + (size_t)row * g.ldo + col) = h;
             if constexpr (DN) {
-              float4 sc;
-              if constexpr (kScvAhead) sc = scv[buf][p];
-              else sc = *reinterpret_cast<const float4 *>(g.dscale + (size_t)g.rowmod[row] * g.gate_stride + col);
+              const float4 sc = scv[buf][p];
               bf16x4 tv;
               tv[0] = (bf16)(h.x * (1.0f + sc.x));
               tv[1] = (bf16)(h.y * (1.0f + sc.y));
@@ -940,7 +930,8 @@ static constexpr DirectCfg kDirect[kDirectConfigs] = {
 
 static int device_cu_count();
 
-// Cost of an unsplit launch (kCfgs), microseconds.
+// Cost of a launch of `slices` blocks per tile over K each (kCfgs; b: a round's
+// fixed part), microseconds.
 static float tile_cost(int c, int M, int N, float K, float b, int slices, int n_cu) {
   const long tiles = (long)((M + kCfgs[c].bm - 1) / kCfgs[c].bm) * ((N + kCfgs[c].bn - 1) / kCfgs[c].bn) * slices;
   const long rounds = (tiles + n_cu - 1) / n_cu;
