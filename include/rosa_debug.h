@@ -88,6 +88,23 @@ rosa_status rosa_debug_attention(rosa_batch *b, const rosa_request *reqs, int32_
 rosa_status rosa_debug_gemm(rosa_batch *b, int32_t which, int32_t layer, const void *a, int32_t M,
                             void *out, const float *gate);
 
+/* A gated-residual projection, the modulated RMSNorm that reads its rows and the
+ * projection that reads the norm, in the forms the layers run (bf16 handles;
+ * ROSA_E_UNSUPPORTED for fp32 ones), on M stacked rows.
+ *   which = 1: h[M][d] += gate * (a[M][n_q*hd] W_o[layer]), then
+ *              out[M][d_mlp] = gelu_tanh(norm W_up[layer])
+ *   which = 3: h[M][d] += gate * (a[M][d_mlp] W_down[layer]), then
+ *              out[M][Q] = norm W_qkv[layer]
+ * with norm = RMSNorm(h) (1 + scale) + shift; a and out DEVICE bf16, h DEVICE
+ * fp32, mod DEVICE fp32 [M][3 d] with row m's shift | scale | gate, all 16-byte
+ * aligned (ROSA_E_INVALID otherwise).  defer: the second projection may complete
+ * the norm (d a multiple of 256 up to 1024, else ROSA_E_UNSUPPORTED).
+ * *form receives how the norm ran: 0 a launch of its own, 1 in the sum of
+ * the first projection's K slices, 2 deferred.  ROSA_E_CAPACITY where the shift
+ * table of M rows would not fit the handle's (L * 128 rows always do). */
+rosa_status rosa_debug_gemm_norm(rosa_batch *b, int32_t which, int32_t layer, const void *a, int32_t M,
+                                 float *h, const float *mod, void *out, int32_t defer, int32_t *form);
+
 /* Force the block configuration of every bf16 projection launched on this
  * handle (rosa_generate_actions and rosa_debug_gemm): cfg in [0, n) where n is
  * returned in *n_configs, or -1 for the built-in cost model (the default).

@@ -1545,6 +1545,60 @@ rosa_status rosa_debug_gemm(rosa_batch *b, int32_t which, int32_t layer, const v
   }
 }
 
+rosa_status rosa_debug_gemm_norm(rosa_batch *b, int32_t which, int32_t layer, const void *a, int32_t M, float *h,
+                                 const float *mod, void *out, int32_t defer, int32_t *form) {
+  if (!b) return ROSA_E_INVALID;
+  try {
+    if (b->poisoned) return fail(b, ROSA_E_DEVICE, "handle is poisoned");
+    const Dims &D = b->dims;
+    if (!b->bf16 || (defer && (D.d % 256 || D.d > 1024 || !b->dn_ss)))
+      return fail(b, ROSA_E_UNSUPPORTED, "bf16 only, deferred norms for widths of 256 n up to 1024");
+    if ((which != 1 && which != 3) || layer < 0 || layer >= D.L || !a || !h || !mod || !out || !form || M < 0 ||
+        M > b->cap.max_action_tokens)
+      return fail(b, ROSA_E_INVALID, "bad gemm arguments");
+    if (((uintptr_t)a | (uintptr_t)h | (uintptr_t)mod | (uintptr_t)out) & 15)
+      return fail(b, ROSA_E_INVALID, "gemm operands must be 16-byte aligned");
+    const int N2 = which == 1 ? D.dff : D.qkv_dim;
+    if (defer && (size_t)M * N2 > (size_t)D.L * kMaxTau * (D.qkv_dim + D.dff))
+      return fail(b, ROSA_E_CAPACITY, "shift table above the handle's");
+    *form = 0;
+    if (M == 0) return ROSA_OK;
+    const int R = b->kb_rows;
+    GemmArgs g{};
+    g.M = M; g.N = D.d; g.epi = kEpiGatedResidual; g.out = h; g.ldo = D.d;
+    g.gate = mod + 2 * D.d; g.gate_stride = 3 * D.d; g.rowmod = b->ident;
+    g.part = b->gemm_part; g.part_floats = b->gemm_part_floats;
+    g.K = g.lda = which == 1 ? D.o_dim : D.dff;
+    g.wt = (uint8_t *)(which == 1 ? b->wt_o : b->wt_down) + (size_t)layer * D.d * g.K * b->esz;
+    void *ws = which == 1 ? b->o : b->g;
+    g.a = ws; g.a_rows = R;
+    if (defer) { g.dt = b->u; g.dt_rows = R; g.dss = b->dn_ss; g.dscale = mod + D.d; }
+    GemmArgs g2{};
+    g2.a = b->u; g2.lda = D.d; g2.a_rows = R; g2.M = M; g2.N = N2; g2.K = D.d; g2.out = out; g2.ldo = N2;
+    g2.epi = which == 1 ? kEpiGelu : kEpiStore;
+    g2.wt = (uint8_t *)(which == 1 ? b->wt_up : b->wt_qkv) + (size_t)layer * N2 * D.d * b->esz;
+    g2.part = b->gemm_part; g2.part_floats = b->gemm_part_floats;
+    const NormArgs nm{mod, 3 * D.d, 0, D.d, D.eps, b->u, R};
+    bool normed = false, deferred = false;
+    hipError_t e = hipSetDevice(b->device);
+    if (e == hipSuccess) e = launch_kb32_pack(a, M, g.K, g.lda, ws, R, b->stream);
+    if (e == hipSuccess) e = launch_gemm(g, true, b->stream, b->gemm_cfg, &nm, &normed, &deferred);
+    if (e == hipSuccess && deferred) {
+      e = launch_tau_gemm(mod, 3 * D.d, 0, M, D.d, g2.wt, 0, N2, nullptr, 0, b->dn_shift, N2, 0, 1, b->stream);
+      g2.css = b->dn_ss; g2.cparts = D.d / 32; g2.cd = D.d; g2.ceps = D.eps; g2.rowmod = b->ident;
+      g2.cshift = b->dn_shift; g2.cshift_stride = N2;
+    } else if (e == hipSuccess && !normed) {
+      e = launch_modnorm(h, M, D.d, D.eps, mod, 3 * D.d, 0, D.d, b->ident, b->u, true, b->stream, R);
+    }
+    if (e == hipSuccess) e = launch_gemm(g2, true, b->stream, b->gemm_cfg);
+    if (e != hipSuccess) return device_fail(b, e, "gemm and norm");
+    *form = deferred ? 2 : normed ? 1 : 0;
+    return ROSA_OK;
+  } catch (...) {
+    return fail(b, ROSA_E_DEVICE, "unexpected exception");
+  }
+}
+
 rosa_status rosa_debug_set_lanes(rosa_batch *b, int32_t n) {
   if (!b) return ROSA_E_INVALID;
   if (n < 0 || n > kMaxLanes) return fail(b, ROSA_E_INVALID, "lane count out of range");

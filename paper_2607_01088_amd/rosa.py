@@ -164,6 +164,8 @@ def load(path: Optional[str] = None) -> C.CDLL:
     lib.rosa_debug_attention.restype = C.c_int
     lib.rosa_debug_gemm.argtypes = [vp, i32, i32, vp, i32, vp, vp]
     lib.rosa_debug_gemm.restype = C.c_int
+    lib.rosa_debug_gemm_norm.argtypes = [vp, i32, i32, vp, i32, vp, vp, vp, i32, C.POINTER(i32)]
+    lib.rosa_debug_gemm_norm.restype = C.c_int
     lib.rosa_debug_set_lanes.argtypes = [vp, i32]
     lib.rosa_debug_set_lanes.restype = C.c_int
     lib.rosa_debug_gemm_config.argtypes = [vp, i32, C.POINTER(i32)]
@@ -431,6 +433,13 @@ class ActionExpert:
     def gemm(self, which: int, layer: int, a, M: int, out, gate=None) -> None:
         self._check(self.lib.rosa_debug_gemm(self.handle, which, layer, a.data_ptr(), M, out.data_ptr(),
                                              None if gate is None else gate.data_ptr()))
+
+    def gemm_norm(self, which: int, layer: int, a, M: int, h, mod, out, defer: bool) -> int:
+        """rosa_debug_gemm_norm: returns the form the norm took (0 launch, 1 slice sum, 2 deferred)."""
+        form = C.c_int32(-1)
+        self._check(self.lib.rosa_debug_gemm_norm(self.handle, which, layer, a.data_ptr(), M, h.data_ptr(), mod.data_ptr(),
+                                                  out.data_ptr(), 1 if defer else 0, C.byref(form)))
+        return form.value
 
     def set_lanes(self, n: int) -> None:
         """Number of concurrent sub-batches (streams) per call; 0: chosen per call,

@@ -270,6 +270,56 @@ def test_projection_default_path(which, M, proj, request):
         assert rel_l2(got[:M].astype(np.float64) - h0[:M], gate * acc) < 1e-5
 
 
+@pytest.mark.parametrize("which,M,cfg", [("hd64_bf16", m, -1) for m in (1, 5, 33, 130)] +
+                         [("pi0_bf16", m, -1) for m in (1, 16, 17, 32, 33, 50, 64, 97, 128, 129, 257, 528, 1023, 1024)] +
+                         [("pi0_bf16", 97, c) for c in range(13)])
+@pytest.mark.parametrize("proj", [1, 3])
+@pytest.mark.parametrize("defer", [False, True])
+def test_projection_norm_projection(which, M, cfg, proj, defer, request):
+    """A gated-residual projection, the norm that reads its rows and the next
+    projection, with the norm in a launch of its own, in the slice sum and
+    deferred (the few-row kernel's and every tile's epilogues), against
+    float64.  Bounds: fp32 sums of up to 4096 products; the norm's rows
+    and the output round to bf16 once each (2^-9 relative at most)."""
+    e, w = request.getfixturevalue(which)
+    sh = e.shape
+    layer = sh.n_layers - 1
+    rng = np.random.default_rng(300 + proj + M)
+    d = sh.d_model
+    K_in = sh.n_q_heads * sh.head_dim if proj == 1 else sh.d_mlp
+    W = (w["w_o"] if proj == 1 else w["w_down"])[layer].astype(np.float64)
+    W2 = (w["w_up"] if proj == 1 else w["w_qkv"])[layer].astype(np.float64)
+    a = bf16_round(rng.standard_normal((M, K_in)).astype(np.float32))
+    h0 = rng.standard_normal((M + 1, d)).astype(np.float32)
+    mod = rng.standard_normal((M, 3, d)).astype(np.float32) * np.float32([0.3, 0.3, 1.0]).reshape(3, 1)
+    h = torch.from_numpy(h0).cuda()
+    a_dev = _tdev(a, "bf16")
+    out = torch.full((M + 1, W2.shape[1]), float("nan"), dtype=a_dev.dtype, device="cuda")
+    try:
+        if cfg >= 0:
+            e.gemm_config(cfg)
+        form = e.gemm_norm(proj, layer, a_dev, M, h, torch.from_numpy(mod).cuda(), out, defer)
+        torch.cuda.synchronize()
+    finally:
+        e.gemm_config(-1)
+    if cfg >= 0:
+        assert form == (2 if defer else 0)
+    else:
+        assert form in ((1, 2) if defer else (0, 1))
+    add = mod[:, 2] * (a.astype(np.float64) @ W)
+    got_h = h.cpu().numpy().astype(np.float64)
+    assert np.array_equal(got_h[M:], h0[M:])
+    assert rel_l2(got_h[:M] - h0[:M], add) < 1e-5
+    h64 = h0[:M] + add
+    u = h64 / np.sqrt((h64 ** 2).mean(axis=1, keepdims=True) + sh.rms_eps) * (1.0 + mod[:, 1]) + mod[:, 0]
+    ref = u @ W2
+    got = _thost(out)
+    assert np.isnan(got[M:]).all()
+    err = rel_l2(got[:M], gelu_tanh(ref) if proj == 1 else ref)
+    print(f"form {form} rel-L2 {err:.2e}", flush=True)
+    assert err < 4e-3, (form, err)
+
+
 # ------------------------------------------------------------------ attention
 
 def _attn_case(e, shapes, seed, fill_q=None, tags=None):
