@@ -196,7 +196,7 @@ def _classify_dispatches(rows):
             cur = "attention"
         elif "gemm_split_reduce" in n:
             cur = prev if prev.startswith("gemm_") else "other"
-        elif "gemm_bf16_kernel" in n:
+        elif "gemm_bf16_kernel" in n or "gemm_direct_kernel" in n:
             if prev in ("attention", "attn_merge"):
                 cur = "gemm_o"
             elif prev == "gemm_up":

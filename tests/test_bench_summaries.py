@@ -49,6 +49,21 @@ def test_classify_dispatches_deferred_norms():
                                                   "gemm_qkv"]
 
 
+def test_classify_dispatches_few_row_products():
+    # One robot: every product but a sliced MLP-down in the few-row kernel, the
+    # norms deferred or in the slice sum.
+    direct = "void rosa::gemm_direct_kernel<1, 2, 16, 4, 0, true>(rosa::GemmArgs, int, int, int)"
+    seq = ["tau_gemm_kernel<4>", "setup_rows_kernel", "in_proj_kernel<32, 4>", "modnorm_kernel", direct,
+           "attention_bf16_kernel", "attn_merge_kernel", direct, direct, "gemm_bf16_kernel<D,3>",
+           "gemm_split_reduce_norm_kernel<8, 1>", direct, "attention_bf16_kernel", "attn_merge_kernel", direct, direct,
+           direct, "modnorm_kernel", "out_proj_euler_kernel", "in_proj_kernel<32, 4>", "modnorm_kernel", direct]
+    role = bench._classify_dispatches(_rows(seq))
+    assert [role[i] for i in range(len(seq))] == ["other", "other", "other", "modnorm", "gemm_qkv", "attention",
+                                                  "attn_merge", "gemm_o", "gemm_up", "gemm_down", "gemm_down",
+                                                  "gemm_qkv", "attention", "attn_merge", "gemm_o", "gemm_up",
+                                                  "gemm_down", "modnorm", "other", "other", "modnorm", "gemm_qkv"]
+
+
 def test_visible_keys_counts_the_prefix_lm_mask():
     # brute force over the mask: token t sees key j iff j < max(P - c, t + 1)
     for P in (1, 5, 17):
