@@ -72,7 +72,7 @@ __device__ __forceinline__ void static_for(F &&f) {
 template <int CPR>
 __device__ __forceinline__ int gswz(int r) { return CPR == 4 ? (r >> 2) & 3 : (r >> 1) & 7; }
 
-template <int MB_, int TN_, int WM_, int WN_, int BK_ = 32, int NST_ = 4, int LA_ = 1>
+template <int MB_, int TN_, int WM_, int WN_, int BK_ = 32, int NST_ = 4, int LA_ = 1, int BACK_ = 0>
 struct GemmTile {
   static constexpr int MB = MB_, TN = TN_, WM = WM_, WN = WN_, NW = WM_ * WN_, NT = 64 * NW;
   static constexpr int MBW = MB / WM;                                   // 32-row blocks per wave
@@ -89,6 +89,12 @@ struct GemmTile {
   // sets (a divisor of the ring's k-steps, so the sets repeat with the ring).
   static constexpr int NKS = BK / 16, LA = LA_, NSET = LA_ < 2 ? 2 : 4;
   static_assert(LA >= 1 && LA <= NKS && LA < NSET && NST * NKS % NSET == 0, "look-ahead");
+  // BACK 0: a stage boundary refills the buffer of the stage just read, so the
+  // block waits there for its own LDS reads of it; 1: the one read before
+  // that (one stage less in flight, no such wait).  The small tiles have too few
+  // MFMAs per k-step to cover that wait (64 x 64 and 64 x 32: 5 - 8% of a launch).
+  static constexpr int BACK = BACK_;
+  static_assert(BACK == 0 || BACK == 1, "refill distance");
   static constexpr int U = (BM + BN) / RPU;                             // 1 KB copies per stage
   static_assert(BK == 32 || BK == 64, "stage K");
   static constexpr int CHI = (U + NW - 1) / NW, CLO = U / NW;           // copies per wave
@@ -177,21 +183,28 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs &g, int m0, int n0,
     for (int i = 0; i < MBW; ++i) fa[f][i] = *reinterpret_cast<const bf16x8 *>(st + arow + i * 32 * ROWB + ph[ks]);
   };
   constexpr int NMF = MBW * TN, NMS = LA * NMF;   // MFMAs per k-step, and per stage after its barrier
+  constexpr int NFL = NST - T::BACK;              // stages in flight or landed after a refill
   // Stage kt in buffer `cur`.  Before k-step NKS - LA, whose look-ahead is the
   // first read of stage kt + 1, the block crosses the stage boundary: the wait
-  // covers this wave's own reads of stage kt and copies of stage kt + 1 (stages
-  // kt + 2 .. kt + NST - 1 may still be in flight); after the barrier both hold
-  // for every wave, so stage kt's buffer is free and takes stage kt + NST.  The
+  // covers this wave's copies of stage kt + 1 (stages kt + 2 .. kt + NFL - 1 may
+  // still be in flight) and, with BACK 0, its own reads of stage kt; after the barrier
+  // both hold for every wave, so the buffer of stage kt (BACK 1: of stage kt - 1, whose
+  // reads every wave's MFMAs have consumed by then) is free and takes stage kt + NFL.  The
   // copies are spread evenly over the stage's remaining MFMAs, so no wave
   // stalls on a burst of them.
   auto stage = [&](auto cur_t, int kt) __attribute__((always_inline)) {
     constexpr int cur = decltype(cur_t)::value;
-    constexpr int nxt = cur + 1 == NST ? 0 : cur + 1;
+    constexpr int nxt = cur + 1 == NST ? 0 : cur + 1, fill = (cur + NFL) % NST;
     static_for<NKS>([&](auto ks_t) __attribute__((always_inline)) {
       constexpr int ks = decltype(ks_t)::value, q = cur * NKS + ks;
       if constexpr (ks == NKS - LA) {
-        if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NST - 2) * CHI));
-        else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NST - 2) * CLO));
+        if constexpr (T::BACK == 0) {
+          if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NFL - 2) * CHI));
+          else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NFL - 2) * CLO));
+        } else {
+          if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NFL - 2) * CHI));
+          else __builtin_amdgcn_s_waitcnt(waitcnt_vm((NFL - 2) * CLO));
+        }
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -207,7 +220,7 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs &g, int m0, int n0,
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int c = 0; c < CHI; ++c)
-              if ((c * NMS) / CHI == (ks - (NKS - LA)) * NMF + i * TN + j) issue_one(L + cur * SBYTES, kt + NST, c);
+              if ((c * NMS) / CHI == (ks - (NKS - LA)) * NMF + i * TN + j) issue_one(L + fill * SBYTES, kt + NFL, c);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -215,12 +228,12 @@ __device__ __forceinline__ void gemm_mainloop(const GemmArgs &g, int m0, int n0,
     });
   };
 
-  // Prologue: stages 0 .. NST - 1 requested, stage 0 landed and its first LA
+  // Prologue: stages 0 .. NFL - 1 requested, stage 0 landed and its first LA
   // k-steps being read.
 #pragma unroll
-  for (int st = 0; st < NST; ++st) issue(L + st * SBYTES, st);
-  if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 1) * CHI));
-  else __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 1) * CLO));
+  for (int st = 0; st < NFL; ++st) issue(L + st * SBYTES, st);
+  if (hi) __builtin_amdgcn_s_waitcnt(waitcnt_vm((NFL - 1) * CHI));
+  else __builtin_amdgcn_s_waitcnt(waitcnt_vm((NFL - 1) * CLO));
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
   static_for<LA>([&](auto ks_t) { read_frags(L, ks_t, ks_t); });
@@ -466,11 +479,20 @@ __global__ void __launch_bounds__(T::NT) gemm_bf16_kernel(GemmArgs g, int nrt, i
   const int per = n_units >> 3, extra = n_units & 7;
   if (q >= per + (x < extra ? 1 : 0)) return;
   const int unit = x * per + min(x, extra) + q;
-  const int tile = unit % n_tiles, slice = unit / n_tiles;
-  const int sidx = min(tile / (nrt * strip), (nct - 1) / strip);
+  // Each division here is a chain of some tens of instructions before the
+  // tile's first copy: only split launches divide by the slices.
+  const int nk = g.K / T::BK;
+  int tile = unit, slice = 0, kt0 = 0, kt1 = nk;
+  if constexpr (EPI == kEpiPartial) {
+    slice = unit / n_tiles;
+    tile = unit - slice * n_tiles;
+    kt0 = nk * slice / ksplit;
+    kt1 = nk * (slice + 1) / ksplit;
+  }
+  const int sidx = tile / (nrt * strip);    // strips before the last are `strip` columns wide
   const int in_strip = tile - sidx * nrt * strip, width = min(strip, nct - sidx * strip);
-  const int m0 = (in_strip / width) * T::BM, n0 = (sidx * strip + in_strip % width) * T::BN;
-  const int nk = g.K / T::BK, kt0 = nk * slice / ksplit, kt1 = nk * (slice + 1) / ksplit;
+  const int row = in_strip / width;
+  const int m0 = row * T::BM, n0 = (sidx * strip + in_strip - row * width) * T::BN;
   f32x16 acc[T::MBW][T::TN];
   NormRows<T> nr;
   if constexpr (DN && EPI != kEpiGatedResidual) gemm_norm_rows<T>(g, m0, nr);
@@ -515,14 +537,14 @@ using Cfg1 = GemmTile<8, 2, 2, 4, 32, 4, 1>;
 using Cfg2 = GemmTile<4, 2, 2, 4, 32, 4, 2>;
 using Cfg3 = GemmTile<6, 1, 2, 4, 32, 4, 1>;
 using Cfg4 = GemmTile<9, 1, 3, 4, 32, 4, 2>;
-using Cfg5 = GemmTile<4, 1, 2, 2, 64, 6, 3>;
+using Cfg5 = GemmTile<4, 1, 2, 2, 64, 6, 3, 1>;
 using Cfg6 = GemmTile<6, 1, 2, 4, 64, 4, 3>;
 using Cfg7 = GemmTile<4, 2, 2, 2, 64, 4, 3>;
 using Cfg8 = GemmTile<5, 1, 1, 4, 64, 4, 3>;
 using Cfg9 = GemmTile<3, 1, 1, 4, 64, 4, 3>;
 using Cfg10 = GemmTile<8, 1, 4, 2, 64, 4, 3>;
-using Cfg11 = GemmTile<2, 1, 2, 2, 64, 8, 1>;
-using Cfg12 = GemmTile<2, 1, 2, 1, 64, 8, 1>;
+using Cfg11 = GemmTile<2, 1, 2, 2, 64, 8, 1, 1>;
+using Cfg12 = GemmTile<2, 1, 2, 1, 64, 8, 1, 1>;
 template <typename T>
 constexpr bool cfg_matches(const GemmCfg &c) { return T::BM == c.bm && T::BN == c.bn && T::BK == c.bk; }
 static_assert(cfg_matches<Cfg0>(kCfgs[0]) && cfg_matches<Cfg1>(kCfgs[1]) && cfg_matches<Cfg2>(kCfgs[2]) &&
@@ -745,9 +767,10 @@ __global__ void __launch_bounds__(64 * KG) gemm_direct_kernel(GemmArgs g, int nr
   const int per = n_tiles >> 3, extra = n_tiles & 7;
   if (q >= per + (x < extra ? 1 : 0)) return;
   const int tile = x * per + min(x, extra) + q;
-  const int sidx = min(tile / (nrt * strip), (nct - 1) / strip);
+  const int sidx = tile / (nrt * strip);
   const int in_strip = tile - sidx * nrt * strip, width = min(strip, nct - sidx * strip);
-  const int m0 = (in_strip / width) * BM, n0 = (sidx * strip + in_strip % width) * BN;
+  const int row0 = in_strip / width;
+  const int m0 = row0 * BM, n0 = (sidx * strip + in_strip - row0 * width) * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int kg = __builtin_amdgcn_readfirstlane(tid >> 6) % KG;
   // This wave's share of K, in steps of 32.
