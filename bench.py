@@ -388,6 +388,9 @@ _CALL_TRACES = {
               "horizon 50, 10 Euler steps, bf16)", "--workload pi0_b1"),
     "tr_b16": ("kernel_trace_factory_first16.md", "one 16-robot call: the first 16 requests of the factory_b256 "
                "batch (horizons 16/50, 5/10 Euler steps, bf16)", "--workload factory_b256 --first 16"),
+    "tr_alt64": ("kernel_trace_alternating_first64.md", "one 64-robot call of the alternating head: the first 64 "
+                 "requests of the factory_b256 batch (horizons 16/50, 5/10 Euler steps, bf16)",
+                 "--workload factory_b256 --first 64 --attention-layout alternating"),
 }
 
 

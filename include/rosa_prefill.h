@@ -107,6 +107,9 @@ typedef struct rosa_prefix_job {
 
 /* Create a handle: validate, upload and repack the weights, allocate
  * workspaces for up to max_jobs jobs and max_tokens prefix tokens per call.
+ * A bf16 handle's workspaces include the products of projections whose K is
+ * split over blocks: 32 bytes per token and column of the widest projection, at
+ * most 64 MiB.
  * hip_stream: a hipStream_t (NULL = the default stream).  Errors as
  * rosa_batch_create; *out is NULL on failure. */
 rosa_status rosa_prefill_create(const rosa_vlm_config *cfg, const rosa_vlm_weights *w, int32_t max_jobs,

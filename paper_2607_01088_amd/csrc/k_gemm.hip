@@ -32,7 +32,8 @@ namespace rosa {
 // 0.26 three ahead, which is what 32 KB take at the 125 GB/s a CU's copies
 // reach).  One barrier per stage, crossed before the first look-ahead into the
 // next stage; by then the whole stage is in registers, so its buffer is
-// refilled at once and NST - 1 stages are in flight or landed.  The copies are
+// refilled at once and NST - 1 stages are in flight or landed (the smallest
+// tiles refill the stage before it, see BACK).  The copies are
 // issued as inline assembly the compiler does not track and the barrier is a
 // bare s_barrier, so the only wait on them is the explicit vmcnt before it.
 //

@@ -200,6 +200,10 @@ constexpr int kMinLaneRequests = 64;  // a batch splits into lanes only with at 
 // mixed ones (12,060 rows, 6,100 late) 68.7 and 73.7, 128 of 50 (6,400) 51.2 and 52.7
 // on one card, 52.7 and 52.0 on another, 200 of 33 (6,600) 51.0 and 50.6, 448 mixed
 // (14,036, 7,250 late) 82.6 and 81.2, 512 of 50 (25,600) 191.7 and 178.9.
+// The better count changes with how the rows happen to fill rounds of tiles, not
+// steadily with the width: over 153 calls of 9 model shapes (4 layers, width 256 to
+// 2048, both layouts, whole and step calls of 128 to 512 requests) this line
+// is 1.1% off the better count on average, always two lanes 2.7%, always one 1.5%.
 constexpr int kMinLateRows = 6200;
 // A call of at most this many rows runs one lane whatever its request count, so
 // that its products may sum K in slices: 128 requests of 1 row 13.6 ms in two lanes
