@@ -121,7 +121,7 @@ rosa_status rosa_debug_gemm_config(rosa_batch *b, int32_t cfg, int32_t *n_config
  * no rounding depends on the lanes, so results are bitwise identical for any
  * lane count; only the overlap of the sub-batches' kernels changes.  n in [1, 4]
  * forces a count; 0, the state of a new handle, lets a bf16 handle take one or
- * two lanes per call by the rows of its late steps, an fp32 one a single lane.
+ * two lanes per call by its steps' mean active rows, an fp32 one a single lane.
  * While per-kernel profiling is enabled every call runs one lane. */
 rosa_status rosa_debug_set_lanes(rosa_batch *b, int32_t n);
 

@@ -194,17 +194,19 @@ constexpr int kMaxSlots = kAttnMaxSlots;
 constexpr int kMaxLanes = 4;
 constexpr int kMinLaneRequests = 64;  // a batch splits into lanes only with at least this many requests per lane
 // Without a forced lane count a call of 2 kMinLaneRequests requests or more runs
-// two lanes if at least this many rows are still active three quarters through
-// its steps.  Two lanes fill each other's gaps but halve every launch (one lane and
-// two, ms): 130 requests of horizon 43 (5,590 rows all along) 45.5 and 49.4, 384
-// mixed ones (12,060 rows, 6,100 late) 68.7 and 73.7, 128 of 50 (6,400) 51.2 and 52.7
-// on one card, 52.7 and 52.0 on another, 200 of 33 (6,600) 51.0 and 50.6, 448 mixed
-// (14,036, 7,250 late) 82.6 and 81.2, 512 of 50 (25,600) 191.7 and 178.9.
-// The better count changes with how the rows happen to fill rounds of tiles, not
-// steadily with the width: over 153 calls of 9 model shapes (4 layers, width 256 to
-// 2048, both layouts, whole and step calls of 128 to 512 requests) this line
-// is 1.1% off the better count on average, always two lanes 2.7%, always one 1.5%.
-constexpr int kMinLateRows = 6200;
+// two lanes if its steps have at least this many active rows on average.  Two lanes
+// fill each other's gaps but halve every launch; one lane does best where the rows of
+// most launches fill one round of 192 x 128 tiles (6,144 rows at N = 1024).  One lane
+// and two (pi0 shape, ms, one card): 192 mixed requests (5,040 rows on average) 42.8 and
+// 43.3, 170 of horizon 33 (5,610) 49.7 and 47.4, 256 mixed (5,740) 47.6 and 48.9,
+// 128 of 48 (6,144) 49.3 and 51.4, 190 of 33 (6,270) 53.1 and 50.4, another 256 mixed
+// (6,350) 53.1 and 51.2, 384 mixed (9,290) 71.2 and 68.5, 256 of 50 (12,800) 94.1 and
+// 89.3.  Over 136 calls on two cards and both layouts the line is 0.15% off the better
+// count on average (always two 1.4%, always one 2.2%); three of four more cards agree, on
+// the fourth two lanes are 1% behind just above the line.  Over 153 calls of 9 model shapes
+// (width 256 to 2048, 4 layers, whole and step calls) it is 1.1% off, always two 2.7%:
+// there the tile rounds fall elsewhere.
+constexpr double kMinTwoLaneRows = 6200;
 // A call of at most this many rows runs one lane whatever its request count, so
 // that its products may sum K in slices: 128 requests of 1 row 13.6 ms in two lanes
 // of unsliced products, 13.8 in one, 11.8 in one with slices; of 4 rows 15.4,
@@ -666,21 +668,23 @@ hipError_t harvest_profile(rosa_batch *b) {
 bool small_call(int n, int64_t rows) { return n < 2 * kMinLaneRequests || rows <= kSmallCallRows; }
 
 // Lanes of a call: one if it is small; else `forced` of them, or (0) one or two
-// by its late rows (see kMinLateRows), and at most one per kMinLaneRequests
-// requests.  The requests are not validated yet: an invalid set gets some count
-// and is refused by the plan, one above the capacity without a look at its requests.
+// by its steps' mean active rows (see kMinTwoLaneRows), and at most one per
+// kMinLaneRequests requests.  The requests are not validated yet: an invalid set gets some
+// count and is refused by the plan, one above the capacity without a look at its requests.
 int call_lanes(const rosa_capacity &cap, const rosa_request *reqs, int n, int max_steps, int forced) {
   if (!reqs || n < 1 || n > cap.max_requests) return 1;
   int64_t rows = 0;
   for (int i = 0; i < n; ++i) rows += std::max(reqs[i].horizon, 0);
   if (small_call(n, rows)) return 1;
   if (forced > 0) return std::min(forced, n / kMinLaneRequests);
-  auto steps = [&](int i) { return std::min((int64_t)reqs[i].num_steps - reqs[i].start_step, (int64_t)max_steps); };
-  int64_t k_max = 0, late = 0;
-  for (int i = 0; i < n; ++i) k_max = std::max(k_max, steps(i));
-  for (int i = 0; i < n; ++i)
-    if (steps(i) > 3 * k_max / 4) late += std::max(reqs[i].horizon, 0);
-  return late >= kMinLateRows ? 2 : 1;
+  int64_t k_max = 0;
+  double row_steps = 0;
+  for (int i = 0; i < n; ++i) {
+    const int64_t k = std::min((int64_t)reqs[i].num_steps - reqs[i].start_step, (int64_t)max_steps);
+    k_max = std::max(k_max, k);
+    row_steps += (double)std::max(reqs[i].horizon, 0) * (double)std::max<int64_t>(k, 0);
+  }
+  return k_max > 0 && row_steps >= kMinTwoLaneRows * (double)k_max ? 2 : 1;
 }
 
 // Copy the plan through a pinned staging buffer into the device plan region.

@@ -9,7 +9,7 @@ import sys
 import pytest
 
 from paper_2607_01088_amd import rosa
-from synthetic import PI0_SHAPE, TINY_SHAPE
+from synthetic import PI0_SHAPE, PRESETS, TINY_SHAPE, make_metadata
 from tests.helpers import ROOT, declared_functions
 
 FAKE = 0x1000   # non-NULL device address; host planning never dereferences it
@@ -112,16 +112,18 @@ def test_plan_lanes_balance_and_cover_every_request():
     ([(50, 10)] * 127, 1),                               # fewer than 64 requests per lane
     ([(49, 10)] * 126 + [(13, 10)] * 2, 2),              # 6,200 rows all along
     ([(49, 10)] * 126 + [(13, 10), (12, 10)], 1),        # 6,199
-    ([(50, 10)] * 124 + [(50, 5)] * 132, 2),             # 6,200 of 12,800 rows late
-    ([(50, 10)] * 123 + [(50, 5)] * 132, 1),             # 6,150
-    ([(50, 10)] * 100 + [(50, 8)] * 156, 2),             # eight of ten steps are late too
-    ([(50, 10)] * 100 + [(50, 7)] * 156, 1),             # seven are not
+    ([(50, 10)] * 84 + [(50, 5)] * 80, 2),               # 6,200 on average: 8,200 early, 4,200 late
+    ([(50, 10)] * 84 + [(50, 5)] * 79, 1),               # 6,175
+    ([(50, 10)] * 48 + [(50, 8)] * 95, 2),               # 6,200
+    ([(50, 10)] * 48 + [(50, 8)] * 94, 1),               # 6,160
     ([(50, 1)] * 124, 1),                                # 6,200 rows of 124 requests
-    ([(50, 10, 9)] * 124 + [(50, 5, 4)] * 132, 2),       # one step each: every row is late
+    ([(50, 10)] * 84 + [(50, 5)] * 44, 1),               # 5,300 of 6,400 rows
+    ([(50, 10, 9)] * 84 + [(50, 5, 4)] * 44, 2),         # one step each: 6,400
+    ([(r.horizon, r.steps) for r in make_metadata(PRESETS["factory_b256"])], 2),   # 6,354
 ])
 def test_plan_lanes_automatic_choice(specs, want):
     """Without a forced count (lanes 0) a call of at least 128 requests takes two
-    lanes where at least 6,200 rows are active three quarters through its steps."""
+    lanes where its steps have at least 6,200 active rows on average."""
     reqs = [req(600, s[0], s[1], start_step=s[2] if len(s) > 2 else 0) for s in specs]
     cap = rosa.capacity(256, 50, 256 * 50, 10, 256 * 600)
     st, lanes = rosa.plan_lanes(PI0_SHAPE, "bf16", cap, reqs, 0)

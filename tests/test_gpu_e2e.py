@@ -172,8 +172,8 @@ def test_factory_first16_deferred_norms(pi0_expert):
 @pytest.mark.timeout(900)
 def test_factory_b256_attention_isolating_both_lanes():
     """The benchmark's whole batch with the MLP removed and the attention gate
-    biased to one, so that attention decides the result: two lanes (forced: on
-    its own this batch takes one) with per-step launch lists, checked on one request per
+    biased to one, so that attention decides the result: two lanes (forced,
+    whatever the automatic choice) with per-step launch lists, checked on one request per
     horizon x steps class in each lane plus the longest and shortest prefix
     among each lane's ten-step requests (the only ones active in steps 5-9)."""
     from paper_2607_01088_amd import rosa
