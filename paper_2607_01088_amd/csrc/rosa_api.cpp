@@ -29,8 +29,10 @@ constexpr int kDeferMaxRows = 1024;
 // layer's weights into the caches, the most bytes of those weights, and the
 // fewest of the CUs' block slots the launch must leave for it.  A step's weights
 // (0.47 GB at the pi0 shape) do not stay in the 256 MB memory-side cache, so each
-// projection reads them from HBM: at the pi0 shape (26 MB a layer) one robot's
-// call 8.13 -> 7.89 ms, 4 robots 10.37 -> 10.18, 16 15.36 -> 14.53, 40 23.25 -> 22.9.
+// projection reads them from HBM: at the pi0 shape (26 MB a layer; off and on, the
+// same on two cards) one robot's call 8.01 -> 7.84 ms, 4 robots 8.34 -> 8.16, 16 11.82 ->
+// 11.67, 32 of horizon 50 22.2 -> 21.85, 40 25.3 -> 24.9, 33 advanced one step 2.05 -> 2.03,
+// 64 of the alternating layout 19.8 -> 19.6.
 // Launches of more rows fill the slots themselves.  A layer that the XCDs' L2s
 // (4 MB each, 32 MB together) cannot hold evicts its own first lines and keeps
 // the launch waiting for what it reads: 50 MB (width 1536) 4.49 -> 4.66 ms for one
