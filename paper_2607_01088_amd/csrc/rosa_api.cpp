@@ -26,20 +26,22 @@ using namespace rosa;
 constexpr int kDeferMaxRows = 1024;
 
 // Most rows a lane-step may have for its attention launch to prefetch the
-// layer's weights into the caches, the most bytes of those weights, and the
-// fewest of the CUs' block slots the launch must leave for it.  A step's weights
-// (0.47 GB at the pi0 shape) do not stay in the 256 MB memory-side cache, so each
-// projection reads them from HBM: at the pi0 shape (26 MB a layer; off and on, the
-// same on two cards) one robot's call 8.01 -> 7.84 ms, 4 robots 8.34 -> 8.16, 16 11.82 ->
-// 11.67, 32 of horizon 50 22.2 -> 21.85, 40 25.3 -> 24.9, 33 advanced one step 2.05 -> 2.03,
-// 64 of the alternating layout 19.8 -> 19.6.
-// Launches of more rows fill the slots themselves.  A layer that the XCDs' L2s
-// (4 MB each, 32 MB together) cannot hold evicts its own first lines and keeps
-// the launch waiting for what it reads: 50 MB (width 1536) 4.49 -> 4.66 ms for one
-// robot and 14.6 -> 14.0 for 40, 86 MB (2048) 3.80 -> 4.23 and 14.3 -> 14.3, 210 MB
-// (4096) 3.57 -> 4.30 and 14.65 -> 14.65.
+// layer's weights into the caches, the most bytes of those weights (up to and above
+// kPrefetchFewRows rows), and the fewest of the CUs' block slots the launch must leave for
+// it.  A step's weights (0.47 GB at the pi0 shape) do not stay in the 256 MB memory-side
+// cache, so each projection reads them from HBM: at the pi0 shape (26 MB a layer; off and
+// on, the same on two cards) one robot's call 8.01 -> 7.84 ms, 4 robots 8.34 -> 8.16, 16
+// 11.82 -> 11.67, 32 of horizon 50 22.2 -> 21.85, 40 25.3 -> 24.9, 33 advanced one step 2.05
+// -> 2.03, 64 of the alternating layout 19.8 -> 19.6.  Launches of more rows fill the slots
+// themselves.  A layer that the XCDs' L2s (4 MB each, 32 MB together) cannot hold evicts
+// its own first lines and keeps a short launch waiting for what it reads; the attention of
+// more rows lasts long enough.  Off and on at 50 MB (width 1536, 4 layers): one robot 1.09 ->
+// 1.16 ms, 16 mixed (530 rows) 3.30 -> 3.35, 33 advanced one step (1,089 rows) 0.587 and
+// 0.587, 100 of horizon 16 5.34 -> 5.23, 128 of 16 6.17 -> 5.73.  86 MB (width 2048) lose at
+// any row count: one robot 1.34 -> 1.47, 40 of 50 7.76 -> 7.85, 100 of 16 7.09 -> 7.26.
 constexpr int kPrefetchMaxRows = 2560;
-constexpr size_t kPrefetchMaxBytes = (size_t)32 << 20;
+constexpr int kPrefetchFewRows = 800;
+constexpr size_t kPrefetchMaxBytesFew = (size_t)32 << 20, kPrefetchMaxBytes = (size_t)64 << 20;
 constexpr int kMinPrefetchBlocks = 64;
 
 // Attention launch order.  The kernel's blocks are persistent: block b runs
@@ -1107,7 +1109,11 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
     }
     const size_t d6 = (size_t)6 * D.d;
     const size_t es = b->esz;
-    const bool prefetch_ok = b->bf16 && ((size_t)D.qkv_dim + D.o_dim + 2 * (size_t)D.dff) * D.d * es <= kPrefetchMaxBytes;
+    const size_t layer_bytes = ((size_t)D.qkv_dim + D.o_dim + 2 * (size_t)D.dff) * D.d * es;
+    auto prefetch_ok = [&](int M) {
+      return b->bf16 && M <= kPrefetchMaxRows &&
+             layer_bytes <= (M <= kPrefetchFewRows ? kPrefetchMaxBytesFew : kPrefetchMaxBytes);
+    };
     for (int k = 0; k < p.Kmax && e == hipSuccess; ++k) {
       for (int li = 0; li < nl && e == hipSuccess; ++li) {
         const Plan::Lane &ln = p.lanes[li];
@@ -1165,7 +1171,7 @@ rosa_status rosa_generate_steps(rosa_batch *b, const rosa_request *reqs, int32_t
               {(uint8_t *)b->wt_up + (size_t)l * D.dff * D.d * es, D.d / 32, (uint32_t)D.dff * 64},
               {(uint8_t *)b->wt_down + (size_t)l * D.d * D.dff * es, D.dff / 32, (uint32_t)D.d * 64},
               {(uint8_t *)b->wt_qkv + (size_t)lq * D.qkv_dim * D.d * es, D.d / 32, (uint32_t)D.qkv_dim * 64}};
-          e = run_attention(b, p, ln, k, l, b->qkv, b->o, st, b->kb_rows, prefetch_ok && M <= kPrefetchMaxRows ? pf : nullptr);
+          e = run_attention(b, p, ln, k, l, b->qkv, b->o, st, b->kb_rows, prefetch_ok(M) ? pf : nullptr);
           if (e != hipSuccess) break;
           GemmArgs go{};
           if (split_ok) { go.part = b->gemm_part; go.part_floats = b->gemm_part_floats; }
