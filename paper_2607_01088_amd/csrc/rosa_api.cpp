@@ -200,7 +200,8 @@ constexpr int kMinLaneRequests = 64;  // a batch splits into lanes only with at 
 // Without a forced lane count a call of 2 kMinLaneRequests requests or more runs
 // two lanes if its steps have at least this many active rows on average.  Two lanes
 // fill each other's gaps but halve every launch; one lane does best where the rows of
-// most launches fill one round of 192 x 128 tiles (6,144 rows at N = 1024).  One lane
+// most launches fill one round of 192 x 128 tiles (6,144 rows at N = 1024), and just above
+// that it starts a second.  One lane
 // and two (pi0 shape, ms, one card): 192 mixed requests (5,040 rows on average) 42.8 and
 // 43.3, 170 of horizon 33 (5,610) 49.7 and 47.4, 256 mixed (5,740) 47.6 and 48.9,
 // 128 of 48 (6,144) 49.3 and 51.4, 190 of 33 (6,270) 53.1 and 50.4, another 256 mixed
@@ -208,9 +209,9 @@ constexpr int kMinLaneRequests = 64;  // a batch splits into lanes only with at 
 // 89.3.  Over 136 calls on two cards and both layouts the line is 0.15% off the better
 // count on average (always two 1.4%, always one 2.2%); three of four more cards agree, on
 // the fourth two lanes are 1% behind just above the line.  Over 153 calls of 9 model shapes
-// (width 256 to 2048, 4 layers, whole and step calls) it is 1.1% off, always two 2.7%:
+// (width 256 to 2048, 4 layers, whole and step calls) it is 1.0% off, always two 2.7%:
 // there the tile rounds fall elsewhere.
-constexpr double kMinTwoLaneRows = 6200;
+constexpr double kMinTwoLaneRows = 6250;
 // A call of at most this many rows runs one lane whatever its request count, so
 // that its products may sum K in slices: 128 requests of 1 row 13.6 ms in two lanes
 // of unsliced products, 13.8 in one, 11.8 in one with slices; of 4 rows 15.4,

@@ -110,20 +110,20 @@ def test_plan_lanes_balance_and_cover_every_request():
 
 @pytest.mark.parametrize("specs,want", [
     ([(50, 10)] * 127, 1),                               # fewer than 64 requests per lane
-    ([(49, 10)] * 126 + [(13, 10)] * 2, 2),              # 6,200 rows all along
-    ([(49, 10)] * 126 + [(13, 10), (12, 10)], 1),        # 6,199
-    ([(50, 10)] * 84 + [(50, 5)] * 80, 2),               # 6,200 on average: 8,200 early, 4,200 late
-    ([(50, 10)] * 84 + [(50, 5)] * 79, 1),               # 6,175
-    ([(50, 10)] * 48 + [(50, 8)] * 95, 2),               # 6,200
-    ([(50, 10)] * 48 + [(50, 8)] * 94, 1),               # 6,160
-    ([(50, 1)] * 124, 1),                                # 6,200 rows of 124 requests
+    ([(49, 10)] * 126 + [(38, 10)] * 2, 2),              # 6,250 rows all along
+    ([(49, 10)] * 126 + [(38, 10), (37, 10)], 1),        # 6,249
+    ([(50, 10)] * 85 + [(50, 5)] * 80, 2),               # 6,250 on average: 8,250 early, 4,250 late
+    ([(50, 10)] * 85 + [(50, 5)] * 79, 1),               # 6,225
+    ([(50, 10)] * 45 + [(50, 8)] * 100, 2),              # 6,250
+    ([(50, 10)] * 45 + [(50, 8)] * 99, 1),               # 6,210
+    ([(50, 1)] * 124, 1),                                # 124 requests
     ([(50, 10)] * 84 + [(50, 5)] * 44, 1),               # 5,300 of 6,400 rows
     ([(50, 10, 9)] * 84 + [(50, 5, 4)] * 44, 2),         # one step each: 6,400
     ([(r.horizon, r.steps) for r in make_metadata(PRESETS["factory_b256"])], 2),   # 6,354
 ])
 def test_plan_lanes_automatic_choice(specs, want):
     """Without a forced count (lanes 0) a call of at least 128 requests takes two
-    lanes where its steps have at least 6,200 active rows on average."""
+    lanes where its steps have at least 6,250 active rows on average."""
     reqs = [req(600, s[0], s[1], start_step=s[2] if len(s) > 2 else 0) for s in specs]
     cap = rosa.capacity(256, 50, 256 * 50, 10, 256 * 600)
     st, lanes = rosa.plan_lanes(PI0_SHAPE, "bf16", cap, reqs, 0)
